@@ -918,8 +918,19 @@ __global__ __launch_bounds__(256) void kinematics_kernel(const double* __restric
 // distance from the tile's centre to each particle at state s_key, in bins of
 // one slot (widened if the spread needs more than kOrderBins).  perm[tile][i]
 // is the i-th particle in that order.
+//
+// Latency bound: a workgroup sorts one tile's particles for one group of runs,
+// and there are tiles x groups of them.  Only the bins the spread covers are
+// cleared and scanned, the scan is a wavefront scan (one thread walking all
+// bins in LDS was 38 us of every order, whatever the particle count), and up
+// to kOrderHeld particles a thread keep their key in registers over the three
+// passes (range, histogram, scatter) instead of computing it again.
+// Measured (a serial scan and three key passes before): one particle, 64 tiles
+// 38.6 -> 6.8 us; 1000 particles, 1024 tiles x 128 groups 4348 -> 675 us.
 constexpr int kOrderBins = 4096;
+constexpr int kOrderHeld = 8;  // keys a thread holds (n_p <= 256 * kOrderHeld)
 
+template <bool HELD>
 __global__ __launch_bounds__(256) void order_kernel(const double* __restrict__ x, int64_t n_p,
                                                     int64_t n_s, int64_t xs_stride,
                                                     int64_t n_tiles, int64_t tile_cells,
@@ -928,78 +939,117 @@ __global__ __launch_bounds__(256) void order_kernel(const double* __restrict__ x
                                                     double inv_c, double inv_dt_det,
                                                     int32_t* __restrict__ perm)
 {
-    __shared__ unsigned hist[kOrderBins];
-    __shared__ double red_lo[256], red_hi[256];
-    __shared__ double ctr[3];
+    __shared__ __align__(16) unsigned hist[kOrderBins];
+    __shared__ double red[2][4];
+    __shared__ unsigned wave_sum[4];
     const int tid = threadIdx.x;
+    const int lane = tid % 64, wave = tid / 64;
     const int64_t tile = blockIdx.x % n_tiles;
     const int64_t group = blockIdx.x / n_tiles;
     // the group's middle state
     const int64_t s_key = min(n_s, group * steps_per_group + steps_per_group / 2);
     const int64_t c0 = tile * tile_cells;
     const int64_t c1 = min(c0 + tile_cells, n_c);
-    if (tid < 3) {
-        double s = 0.0;
-        for (int64_t c = c0; c < c1; ++c)
-            s += cells[3 * c + tid];
-        ctr[tid] = s / (double)(c1 - c0);
-    }
-    for (int i = tid; i < kOrderBins; i += 256)
-        hist[i] = 0u;
-    __syncthreads();
+    double ctr[3] = {0.0, 0.0, 0.0};  // the tile's centre (uniform: scalar loads)
+    for (int64_t c = c0; c < c1; ++c)
+#pragma unroll
+        for (int k = 0; k < 3; ++k)
+            ctr[k] += cells[3 * c + k];
+#pragma unroll
+    for (int k = 0; k < 3; ++k)
+        ctr[k] /= (double)(c1 - c0);
     const int64_t stride = xs_stride;
     const int64_t base = s_key * n_p;
-    const double cx = ctr[0], cy = ctr[1], cz = ctr[2];
     auto key = [&](int64_t p) {
-        const double d0 = cx - x[base + p];
-        const double d1 = cy - x[base + p + stride];
-        const double d2 = cz - x[base + p + 2 * stride];
+        const double d0 = ctr[0] - x[base + p];
+        const double d1 = ctr[1] - x[base + p + stride];
+        const double d2 = ctr[2] - x[base + p + 2 * stride];
         return __builtin_sqrt(d0 * d0 + d1 * d1 + d2 * d2) * (inv_c * inv_dt_det);
     };
+    double held[kOrderHeld];
     double lo = 1e300, hi = -1e300;
-    for (int64_t p = tid; p < n_p; p += 256) {
-        const double k = key(p);
+    auto range = [&](double k) {
         if (k == k) {
             lo = fmin(lo, k);
             hi = fmax(hi, k);
         }
-    }
-    red_lo[tid] = lo;
-    red_hi[tid] = hi;
-    __syncthreads();
-    for (int s = 128; s > 0; s >>= 1) {
-        if (tid < s) {
-            red_lo[tid] = fmin(red_lo[tid], red_lo[tid + s]);
-            red_hi[tid] = fmax(red_hi[tid], red_hi[tid + s]);
+    };
+    if constexpr (HELD) {
+#pragma unroll
+        for (int i = 0; i < kOrderHeld; ++i) {
+            const int64_t p = tid + 256 * i;
+            if (p < n_p) {
+                held[i] = key(p);
+                range(held[i]);
+            }
         }
-        __syncthreads();
+    } else {
+        for (int64_t p = tid; p < n_p; p += 256)
+            range(key(p));
     }
-    lo = red_lo[0];
-    hi = red_hi[0];
+    for (int m = 32; m > 0; m >>= 1) {
+        lo = fmin(lo, __shfl_xor(lo, m));
+        hi = fmax(hi, __shfl_xor(hi, m));
+    }
+    if (lane == 0) {
+        red[0][wave] = lo;
+        red[1][wave] = hi;
+    }
+    __syncthreads();
+    lo = fmin(fmin(red[0][0], red[0][1]), fmin(red[0][2], red[0][3]));
+    hi = fmax(fmax(red[1][0], red[1][1]), fmax(red[1][2], red[1][3]));
     const double span = hi > lo ? hi - lo : 0.0;
     const double width = span < (double)(kOrderBins - 1) ? 1.0 : span / (double)(kOrderBins - 1);
-    auto bin_of = [&](int64_t p) {
-        const double k = key(p);
-        double b = (k - lo) / width;
-        b = (b == b) ? fmin(fmax(b, 0.0), (double)(kOrderBins - 1)) : (double)(kOrderBins - 1);
-        return (int)b;
-    };
-    for (int64_t p = tid; p < n_p; p += 256)
-        atomicAdd(&hist[bin_of(p)], 1u);
+    // bins in use; the last one also takes the particles without a key (NaN)
+    const int last = (int)fmin(span / width, (double)(kOrderBins - 2)) + 1;
+    const int n_bins = min(kOrderBins, (last + 1 + 1023) / 1024 * 1024);  // four a thread
+    for (int i = tid; i < n_bins; i += 256)
+        hist[i] = 0u;
     __syncthreads();
-    if (tid == 0) {  // exclusive scan (4096 entries, once per tile)
-        unsigned run = 0;
-        for (int i = 0; i < kOrderBins; ++i) {
-            const unsigned h = hist[i];
-            hist[i] = run;
-            run += h;
-        }
+    auto bin_of = [&](double k) {
+        const double b = (k - lo) / width;
+        return (b == b) ? (int)fmin(fmax(b, 0.0), (double)last) : last;
+    };
+    if constexpr (HELD) {
+#pragma unroll
+        for (int i = 0; i < kOrderHeld; ++i)
+            if (tid + 256 * i < n_p)
+                atomicAdd(&hist[bin_of(held[i])], 1u);
+    } else {
+        for (int64_t p = tid; p < n_p; p += 256)
+            atomicAdd(&hist[bin_of(key(p))], 1u);
     }
     __syncthreads();
+    // exclusive scan, 1024 bins a round: four consecutive ones a thread
+    unsigned before = 0u;  // particles in the rounds before
+    for (int r = 0; r < n_bins; r += 1024) {
+        uint4* h4 = reinterpret_cast<uint4*>(hist + r) + tid;
+        const uint4 h = *h4;
+        const unsigned own = h.x + h.y + h.z + h.w;
+        unsigned incl = own;
+        for (int m = 1; m < 64; m <<= 1) {
+            const unsigned t = __shfl_up(incl, m);
+            incl += lane >= m ? t : 0u;
+        }
+        if (lane == 63)
+            wave_sum[wave] = incl;
+        __syncthreads();
+        unsigned off = before + incl - own;
+        for (int w = 0; w < wave; ++w)
+            off += wave_sum[w];
+        before += wave_sum[0] + wave_sum[1] + wave_sum[2] + wave_sum[3];
+        *h4 = make_uint4(off, off + h.x, off + h.x + h.y, off + h.x + h.y + h.z);
+        __syncthreads();
+    }
     int32_t* out = perm + (group * n_tiles + tile) * n_p;
-    for (int64_t p = tid; p < n_p; p += 256) {
-        const unsigned pos = atomicAdd(&hist[bin_of(p)], 1u);
-        out[pos] = (int32_t)p;
+    if constexpr (HELD) {
+#pragma unroll
+        for (int i = 0; i < kOrderHeld; ++i)
+            if (tid + 256 * i < n_p)
+                out[atomicAdd(&hist[bin_of(held[i])], 1u)] = tid + 256 * i;
+    } else {
+        for (int64_t p = tid; p < n_p; p += 256)
+            out[atomicAdd(&hist[bin_of(key(p))], 1u)] = (int32_t)p;
     }
 }
 
@@ -1947,7 +1997,8 @@ hipError_t launch_kinematics(const DepositJob& job, int mode, hipStream_t s)
 
 hipError_t launch_order(const DepositJob& job, hipStream_t s)
 {
-    hipLaunchKernelGGL(order_kernel, dim3((unsigned)(job.n_tiles * job.n_groups)), dim3(256), 0, s,
+    auto kernel = job.n_p <= 256 * kOrderHeld ? order_kernel<true> : order_kernel<false>;
+    hipLaunchKernelGGL(kernel, dim3((unsigned)(job.n_tiles * job.n_groups)), dim3(256), 0, s,
                        job.x, job.n_p, job.n_s, job.xs_stride, job.n_tiles,
                        (int64_t)job.tile_cells, job.runs_per_group * job.run_l,
                        job.cells, job.n_c, job.inv_c, job.inv_dt_det, job.perm);
