@@ -86,14 +86,17 @@ constexpr int kCounters = 4;  // a detector's device counters (DepositJob::count
 #ifndef RADIO_RING_LARGE
 #define RADIO_RING_LARGE 64
 #endif
-// segments a large-ring workgroup stages at most per batch (longer runs are
-// staged in parts of this length): what the large ring's span allows
-#ifndef RADIO_LARGE_STAGE
-#define RADIO_LARGE_STAGE 16
-#endif
 constexpr int kRingSmall = RADIO_RING_SMALL;
 constexpr int kRingLarge = RADIO_RING_LARGE;
-constexpr int kLargeStage = RADIO_LARGE_STAGE;
+// A tile's ring choice (DepositJob::ring_sel): the small ring, or kRingSel64 + h,
+// the large one with a run staged in 2^h stretches (arrivals so sparse that a
+// longer one spans more slots than the large ring); with kRingSelJumps the
+// large ring holds field jumps instead of slot values.
+constexpr int kRingSel16 = 0;
+constexpr int kRingSel64 = 1;
+constexpr int kRingSelShift = 7;  // mask of kRingSel64 + h
+constexpr int kRingSelJumps = 8;
+constexpr int kMaxPartShift = 4;
 
 // One (detector, chunk) deposit as the kernels see it.  Sizes are 64-bit; the
 // host runtime has validated every pointer and size before filling this in.
@@ -108,7 +111,7 @@ struct DepositJob {
     const double* q;                // [n_p] or nullptr (all -1)
     void* recs;                     // workspace [n_p][n_s+1] records of the job's mode
     int32_t* perm;                  // workspace [n_groups][n_tiles][n_p]: particle orders
-    uint8_t* ring_sel;              // workspace [n_tiles]: 1 where a tile takes the large ring
+    uint8_t* ring_sel;              // workspace [n_tiles]: the tiles' ring choices (kRingSel...)
     const double* far;              // far-field detector: [n_c][4] n_cell, R_cell; else nullptr
     double vscale;                  // 1, or 0 for an acceleration-only detector
     int64_t hold;                   // field a segment holds: 0 current, 1 previous, 2 linear
@@ -169,16 +172,18 @@ void set_parts(DepositJob& job, int64_t parts);
 // re-sorted along it.  max_order_groups is how many orders fit the budget
 // (budget_mib, or when 0 the size of the chunk's state records and at least
 // 1 GiB); set_groups spreads the job's runs over at most that many groups.
-// Chunks of fewer than 16 batches of particles keep one order.
+// Chunks of fewer than two batches of particles keep one order.
 int64_t max_order_groups(const DepositJob& job, size_t rec_bytes, int64_t budget_mib);
 void set_groups(DepositJob& job, int64_t max_groups);
 // Runs per order group that a deposit keeps to, by depositing a longer chunk
 // in time slices whose orders fit the budget; particles below which a chunk
-// keeps a single order (16 batches of the job's shape).
+// keeps a single order (two batches of the job's shape: with fewer there is nothing to
+// sort; uneven sets of 54-434 particles gained 1.3% from orders below 16 batches, whose
+// arrival offsets drift apart over a long chunk too).
 constexpr int64_t kRunsPerGroup = 2;
 inline int64_t min_group_particles(const DepositJob& job)
 {
-    return 16 * (int64_t)job.groups;
+    return 2 * (int64_t)job.groups;
 }
 
 hipError_t launch_zero(double* p, int64_t n, hipStream_t s);

@@ -256,6 +256,25 @@ __device__ __forceinline__ void global_add_pair(RADIO_GLOBAL float* row, int j, 
                                __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
 }
 
+// one component k of slot j
+__device__ __forceinline__ void global_add_one(RADIO_GLOBAL double* row, int j, int k, double v)
+{
+    __hip_atomic_fetch_add(row + (int64_t)j * 6 + k, v, __ATOMIC_RELAXED,
+                           __HIP_MEMORY_SCOPE_AGENT);
+}
+
+// the same into the compensated pair: v split into hi and lo
+__device__ __forceinline__ void global_add_one(RADIO_GLOBAL float* row, int j, int k, double v)
+{
+    RADIO_GLOBAL float* q = row + (int64_t)j * 12 + k;
+    const float hi = (float)v;
+    const float lo = (float)(v - (double)hi);
+    const float old =
+        __hip_atomic_fetch_add(q, hi, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    __hip_atomic_fetch_add(q + 6, two_sum_err(old, hi, old + hi) + lo, __ATOMIC_RELAXED,
+                           __HIP_MEMORY_SCOPE_AGENT);
+}
+
 // position of slot j >= 0 in a ring of R slots
 template <int R>
 __device__ __forceinline__ int ring_pos(int j)
@@ -274,14 +293,16 @@ __device__ __forceinline__ int ring_pos(int j)
 // for compensated single accumulation (Acc = float) the pair hi[6], lo[6] per
 // slot, which a slot leaving the ring reaches as the double split into hi and
 // lo, and a bypassing emission as itself (two-sum into the pair).
-template <typename Acc, int R>
-struct CellSink;
-
-template <int R>
-struct CellSink<double, R> {
+// The rings of a tile's TC cells lie in LDS as [slot][component][cell]: an
+// instruction's lanes hold 16 different cells, which then never share a bank,
+// whatever slots they are in (with a cell's slots together and a padded stride
+// the sheet above took 241 ms instead of 180, the undulator ensemble 107 instead
+// of 102).
+template <typename Acc, int R, int TC>
+struct CellSink {
     static constexpr int W = 6;  // values per ring slot
     RADIO_LDS double* ring;
-    RADIO_GLOBAL double* row;
+    RADIO_GLOBAL Acc* row;  // double, or hi[6], lo[6] per slot
     int base;
     int n_t;
     unsigned* n_bypass;
@@ -290,41 +311,19 @@ struct CellSink<double, R> {
     template <typename F>
     __device__ __forceinline__ void flush(int j, const F a[6]) const
     {
-        double v[6];
-#pragma unroll
-        for (int k = 0; k < 6; ++k)
-            v[k] = (double)a[k];
         if ((unsigned)(j - base) < (unsigned)R) {
-            RADIO_LDS double* q = ring + ring_pos<R>(j) * W;
+            RADIO_LDS double* q = ring + ring_pos<R>(j) * (W * TC);
 #pragma unroll
             for (int k = 0; k < 6; ++k)
-                __hip_atomic_fetch_add(q + k, v[k], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
-        } else if ((unsigned)j < (unsigned)n_t) {
-            *n_bypass += 1u;
-            global_add(row, j, v);
-        }
-    }
-};
-
-template <int R>
-struct CellSink<float, R> {
-    static constexpr int W = 6;  // ring values per slot
-    RADIO_LDS double* ring;
-    RADIO_GLOBAL float* row;      // hi[6], lo[6] per slot
-    int base;
-    int n_t;
-    unsigned* n_bypass;
-    __device__ __forceinline__ void flush(int j, const float a[6]) const
-    {
-        if ((unsigned)(j - base) < (unsigned)R) {
-            RADIO_LDS double* q = ring + ring_pos<R>(j) * W;
-#pragma unroll
-            for (int k = 0; k < 6; ++k)
-                __hip_atomic_fetch_add(q + k, (double)a[k], __ATOMIC_RELAXED,
+                __hip_atomic_fetch_add(q + k * TC, (double)a[k], __ATOMIC_RELAXED,
                                        __HIP_MEMORY_SCOPE_WORKGROUP);
         } else if ((unsigned)j < (unsigned)n_t) {
             *n_bypass += 1u;
-            global_add(row, j, a);
+            Acc v[6];
+#pragma unroll
+            for (int k = 0; k < 6; ++k)
+                v[k] = (Acc)a[k];
+            global_add(row, j, v);
         }
     }
 };
@@ -575,6 +574,124 @@ __device__ __forceinline__ void add_segment_linear(Carry<T>& C, const Sink& sink
         }
     } else {
         add_segment_linear_general(C, sink, n_t, a, b, Fa, dF, inv_len, n_back, n_clip);
+    }
+}
+
+// ---------------------------------------------------------------------------
+// the large ring: field jumps
+// ---------------------------------------------------------------------------
+
+// Where arrivals cross a slot or more per segment, a segment's deposit is cheaper
+// as the jumps of the held field at its two ends than as one value per slot it
+// touches.  With f = u - floor(u), a field F held from u on is worth F (1 - f)
+// in slot floor(u) and F in every later one: F (1 - f) added to the slot
+// difference D[floor(u)] and F f to D[floor(u) + 1].  A run of segments that
+// meet end to end deposits, at each state, only the jump from one segment's
+// field to the next's, two slots of six adds whatever the slots between; the
+// large ring therefore holds differences, and the values (the running sums
+// along the slots) are formed when slots leave it.  Plasma-mirror sheet, 1.6
+// slots a segment, 1e5 electrons x 16 steps x 128 x 128 cells: 218 ms with values,
+// 179 with jumps; at about one slot a segment (run-time blocks) values win, 21
+// against 25 ms.
+// A run's jumps add up to nothing beyond its last slot, so at the end of a
+// batch the ring's differences do too, and a ring can be emptied at any slot by
+// carrying the running sum over (forward moves) or dropping it (none is left).
+// Sums and differences are double.  A sum of jumps keeps ~1e-16 of the largest
+// field it has seen; a count of the runs that touch a slot, held the same way,
+// says where none does, and there the sum starts again from zero.  What is left
+// is far below the rounding of a single-precision field, so the mixed modes
+// deposit this way; the double mode, whose results are
+// that accurate slot by slot, keeps slot values (with jumps its worst cell of
+// random trajectories was 2.9e-12 of its norm off, with values 2e-13), and so
+// does the linear hold, whose field changes within a segment.
+//
+// Segments that leave the ring, run backward, start or end on a NaN, or hold a
+// field that is not of ordinary size go through `jump_general`: what lies
+// outside the ring is added to the detector slot by slot; a backward segment
+// holds the negated field between its ends taken in order (the same deposit);
+// a field that is not finite is added to its own slots only, and to the ring as
+// none, since a jump reaches every later slot.
+template <int M, int HOLD>
+constexpr bool jumps = M != kModeF64 && HOLD != 2;
+
+template <typename T>
+__device__ __forceinline__ bool ordinary(const T F[6], bool pot)
+{
+    // the field's B is n x E with |n| <= 1, so E bounds it; potentials: A and phi
+    T m = fabs(F[0]) + fabs(F[1]) + fabs(F[2]);
+    if (pot)
+        m += fabs(F[3]);
+    return m < (sizeof(T) == 8 ? T(1e290) : T(1e30));
+}
+
+// F held over [lo, hi] (0 <= lo, hi <= n_t) straight into the detector
+template <typename T, typename Acc>
+__device__ __forceinline__ void direct_add(RADIO_GLOBAL Acc* row, double lo, double hi,
+                                           const T F[6], unsigned& n_bypass)
+{
+    for (double fl = floor(lo); fl < hi; fl += 1.0) {
+        const Acc w = Acc(fmin(fl + 1.0, hi) - fmax(fl, lo));
+        Acc a[6];
+#pragma unroll
+        for (int k = 0; k < 6; ++k)
+            a[k] = (Acc)F[k] * w;
+        n_bypass += 1u;
+        global_add(row, (int)fl, a);
+    }
+}
+
+// u clamped to the ring's span [wlo, whi] (a NaN to wlo: its segments hold nothing)
+__device__ __forceinline__ double ring_clamp(double u, double wlo, double whi)
+{
+    return u > wlo ? (u < whi ? u : whi) : wlo;
+}
+
+// The general case of a segment between a and b: counts it, adds what the ring
+// does not take to the detector, and leaves in F the field the ring holds.
+template <typename T, typename Acc>
+__device__ __forceinline__ void jump_general(RADIO_GLOBAL Acc* row, double a, double b,
+                                             double wlo, double whi, int n_t, bool pot, T F[6],
+                                             unsigned& n_back, unsigned& n_clip,
+                                             unsigned& n_bypass)
+{
+    const double ntd = (double)n_t;
+    n_back += (b < a) ? 1u : 0u;
+    n_clip += clipped(a, b, ntd);
+    double lo, hi;
+    clamp_segment(a, b, ntd, lo, hi);
+    T sign = T(b < a ? -1 : 1);
+    if (!(lo < hi)) {  // empty, entirely outside, or NaN
+        sign = T(0);
+    } else if (!ordinary(F, pot)) {
+        direct_add(row, lo, hi, F, n_bypass);
+        sign = T(0);
+    } else {
+        if (lo < wlo)
+            direct_add(row, lo, fmin(hi, wlo), F, n_bypass);
+        if (hi > whi)
+            direct_add(row, fmax(lo, whi), hi, F, n_bypass);
+        if (hi <= wlo || lo >= whi)
+            sign = T(0);
+    }
+#pragma unroll
+    for (int k = 0; k < 6; ++k)
+        F[k] = sign == T(0) ? T(0) : sign * F[k];
+}
+
+// The jump d at u (u >= 0, floor(u) and floor(u) + 1 in the ring) into the ring
+template <int R, int TC>
+__device__ __forceinline__ void add_jump(RADIO_LDS double* ring, double u, const double d[6])
+{
+    static_assert((R & (R - 1)) == 0, "ring positions by mask");
+    const int j = (int)u;
+    const double f = __builtin_amdgcn_fract(u);
+    RADIO_LDS double* q0 = ring + (j & (R - 1)) * (6 * TC);
+    RADIO_LDS double* q1 = ring + ((j + 1) & (R - 1)) * (6 * TC);
+#pragma unroll
+    for (int k = 0; k < 6; ++k) {
+        const double t = d[k] * f;
+        __hip_atomic_fetch_add(q0 + k * TC, d[k] - t, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
+        __hip_atomic_fetch_add(q1 + k * TC, t, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
     }
 }
 
@@ -1053,16 +1170,35 @@ __global__ __launch_bounds__(256) void order_kernel(const double* __restrict__ x
     }
 }
 
-// For every tile, whether its batches take the large slot ring.  The small
-// ring keeps four workgroups on a CU, the large one two, so the large ring
-// pays only where the small one would send many emissions to HBM.  The
-// kernel replays sampled batches (the first and the middle run, at eight
-// places of the tile's particle order) at the tile's first cell: it places
-// a small ring the way the deposit does (below the batch's earliest start)
-// and counts the slots a lane would emit outside it.  Above kRingBypassLimit
-// such emissions per interaction the tile takes the large ring.  Only speed
-// depends on this choice: emissions outside a ring go to HBM directly.
-constexpr double kRingBypassLimit = 0.05;   // emissions to HBM per interaction
+// For every tile, the ring its batches take (DepositJob::ring_sel).  The small
+// ring keeps four or five workgroups on a CU, the large one two, so the large ring
+// pays only where the small one would send many emissions to HBM.  The kernel
+// replays sampled batches (runs spread over the chunk, places spread over the
+// tile's particle order) at the tile's first cell: it places the rings the way
+// the deposit does (below the batch's earliest start), counts the slots a lane
+// would emit outside them, and takes the cheapest by the estimates below.  The
+// large ring's runs are staged in halves, quarters, ... where a whole one would
+// outgrow it: a shorter stretch pays a batch's staging and ring move for fewer
+// segments, and helps only where it is the run, not the spread of the batch's
+// particles, that is too long.  Only speed depends on this choice.
+//
+// Estimates, in picoseconds of the whole device per interaction, E the slots a
+// run emits per segment, fitted to mixed-precision deposits (doubles cost more on
+// either side): undulator ensemble E 0.5, small ring, 2.9 ps with 0.3% outside;
+// uneven undulator sets E 0.8, 5 ps in the large ring against 18 in the small one
+// with 4% outside; plasma-mirror sheet E 1.7, 6.8 ps with jumps, 8.3 with values;
+// the sheet sampled at 6.5 slots a segment, L = 2: 34 ps with values, 39 with
+// jumps, and 830 where runs of 16 segments outgrew the ring.
+constexpr double kSmallCost = 3.3, kSmallSlot = 1.0;  // small ring: 3.3 + 1.0 E
+// large ring, a run staged in stretches of L segments: of values 2.6 + 3.0 E + 15/L,
+// of jumps 5 + 40/L whatever E (its move adds up a cell's slots one by one)
+constexpr double kLargeCost = 2.6, kLargeSlot = 3.0, kLargeBatch = 15.0;
+constexpr double kJumpCost = 5.0, kJumpBatch = 40.0;
+// a slot outside the ring (of jumps: by the general path)
+constexpr double kOutsideSlot = 80.0, kOutsideJump = 300.0;
+constexpr int kMaxRun = 16;
+static_assert(shape_run(0) <= kMaxRun && shape_run(1) <= kMaxRun && shape_run(2) <= kMaxRun,
+              "sampled runs");
 
 __global__ __launch_bounds__(256) void ring_choice_kernel(const char* __restrict__ recs,
                                                           int64_t rec_size,
@@ -1075,29 +1211,34 @@ __global__ __launch_bounds__(256) void ring_choice_kernel(const char* __restrict
                                                           int64_t s0, double dt, double t0,
                                                           double inv_dt_det, double inv_c,
                                                           int64_t n_t, int tile_cells, int groups,
-                                                          int run_l, uint8_t* __restrict__ sel)
+                                                          int run_l, int max_shift, int jumps_ok,
+                                                          uint8_t* __restrict__ sel)
 {
-    // one thread per sampled particle: 256 / groups sampled batches, half of them
-    // in the first run and half in the middle one
+    // one thread per sampled particle: 256 / groups sampled batches
     const int n_samples = 256 / groups;
-    const int kChoiceBatches = n_samples / 2;
-    __shared__ int start[64];
-    __shared__ unsigned out_count, segs;
+    // lowest slot of a sampled batch at each state of the run
+    __shared__ int start[64][kMaxRun + 1];
+    __shared__ unsigned out_count, emitted, segs, far_count[kMaxPartShift + 1];
     const int tid = threadIdx.x;
     const int64_t tile = blockIdx.x;
     const int64_t c0 = tile * tile_cells;
-    if (tid < n_samples)
-        start[tid] = INT_MAX;
+    for (int i = tid; i < n_samples * (kMaxRun + 1); i += 256)
+        (&start[0][0])[i] = INT_MAX;
+    if (tid <= kMaxPartShift)
+        far_count[tid] = 0u;
     if (tid == 0) {
         out_count = 0u;
+        emitted = 0u;
         segs = 0u;
     }
     const int smp = tid / groups;  // sampled batch
     const int gg = tid % groups;   // particle within it
     const int64_t n_states = n_s + 1;
     const int64_t n_batches = (n_p + groups - 1) / groups;
-    const int64_t run = (smp < kChoiceBatches) ? 0 : n_runs / 2;
-    const int64_t bt = (2 * (int64_t)(smp % kChoiceBatches) + 1) * n_batches / (2 * kChoiceBatches);
+    // spread over the runs by the golden ratio, which meets no period of the motion
+    const double at = 0.6180339887498949 * (double)smp;
+    const int64_t run = min((int64_t)((at - floor(at)) * (double)n_runs), n_runs - 1);
+    const int64_t bt = (2 * (int64_t)smp + 1) * n_batches / (2 * n_samples);
     const int64_t pi = bt * groups + gg;
     const int64_t s_a = run * run_l;
     const int len = (int)min((int64_t)run_l, n_s - s_a);
@@ -1106,9 +1247,10 @@ __global__ __launch_bounds__(256) void ring_choice_kernel(const char* __restrict
     const double* fc = far ? far + 4 * c0 : nullptr;
     const int32_t* order = perm + ((run / runs_per_group) * n_tiles + tile) * n_p;  // once a thread
     const char* pr = on ? recs + ((int64_t)order[pi] * n_states + s_a) * rec_size : nullptr;
-    // position of state k of this lane's particle: the first three doubles of its record
-    auto pos = [&](int k) { return reinterpret_cast<const double*>(pr + (int64_t)k * rec_size); };
-    auto slot_of = [&](const double* x, int64_t st) {
+    // slot of state k of this lane's particle (its position: the first three
+    // doubles of its record)
+    auto slot_of = [&](int k) {
+        const double* x = reinterpret_cast<const double*>(pr + (int64_t)k * rec_size);
         double dist;
         if (fc) {
             dist = fc[3] - (x[0] * fc[0] + x[1] * fc[1] + x[2] * fc[2]);
@@ -1116,36 +1258,78 @@ __global__ __launch_bounds__(256) void ring_choice_kernel(const char* __restrict
             const double d0 = xc[0] - x[0], d1 = xc[1] - x[1], d2 = xc[2] - x[2];
             dist = __builtin_sqrt(d0 * d0 + d1 * d1 + d2 * d2);
         }
-        const double u = ((t_first + (double)(s0 + st) * dt) + dist * inv_c - t0) * inv_dt_det;
-        return (u == u) ? fmin(fmax(u, -2.0), (double)n_t + 2.0) : -2.0;
+        const double u =
+            ((t_first + (double)(s0 + s_a + k) * dt) + dist * inv_c - t0) * inv_dt_det;
+        return (int)floor((u == u) ? fmin(fmax(u, -2.0), (double)n_t + 2.0) : -2.0);
     };
     __syncthreads();
     if (on)
-        atomicMin(&start[smp], (int)floor(slot_of(pos(0), s_a)));
+        for (int k = 0; k <= len; ++k)
+            atomicMin(&start[smp][k], slot_of(k));
     __syncthreads();
     if (on) {
-        // the small ring of this batch, placed as the deposit places it
-        const int base = (int)fmin(fmax((double)start[smp] - (double)kRingMargin, 0.0),
-                                   fmax((double)(n_t - kRingSmall), 0.0));
-        unsigned outside = 0u;
-        auto emit = [&](int j) {
-            if (j >= 0 && j < n_t && (j < base || j >= base + kRingSmall))
-                ++outside;
+        // where a ring of R slots starts that is placed at state k, ending `spare`
+        // slots past the window
+        auto base_at = [&](int k, int R, int spare) {
+            return (int)fmin(fmax((double)start[smp][k] - (double)kRingMargin, 0.0),
+                             fmax((double)(n_t - R + spare), 0.0));
         };
-        int J = (int)floor(slot_of(pos(0), s_a));
+        const int base = base_at(0, kRingSmall, 0);
+        unsigned outside = 0u, all = 0u, far_segs[kMaxPartShift + 1] = {};
+        auto emit = [&](int j) {
+            if (j >= 0 && j < n_t) {
+                ++all;
+                outside += (j < base || j >= base + kRingSmall) ? 1u : 0u;
+            }
+        };
+        int J = slot_of(0);
         for (int k = 1; k <= len; ++k) {
-            const int jk = (int)floor(slot_of(pos(k), s_a + k));
+            const int jk = slot_of(k);
             for (int j = min(J, jk); j < max(J, jk); ++j)  // slots the lane leaves
                 emit(j);
+#pragma unroll
+            for (int h = 0; h <= kMaxPartShift; ++h)  // the large ring, by length of stretch
+                if (h <= max_shift && jk >= 0 && jk < n_t) {
+                    const int part = max(run_l >> h, 1);
+                    const int b = base_at((k - 1) / part * part, kRingLarge, 2);
+                    far_segs[h] += (jk < b || jk > b + kRingLarge - 2) ? 1u : 0u;
+                }
             J = jk;
         }
         emit(J);  // the run's last slot
         atomicAdd(&out_count, outside);
+        atomicAdd(&emitted, all);
         atomicAdd(&segs, (unsigned)len);
+#pragma unroll
+        for (int h = 0; h <= kMaxPartShift; ++h)
+            if (far_segs[h])
+                atomicAdd(&far_count[h], far_segs[h]);
     }
     __syncthreads();
-    if (tid == 0)
-        sel[tile] = (segs > 0u && (double)out_count > kRingBypassLimit * (double)segs) ? 1 : 0;
+    if (tid == 0) {
+        int choice = kRingSel16;
+        if (segs > 0u) {
+            const double n = (double)segs;
+            const double E = (double)emitted / n;
+            double best = kSmallCost + kSmallSlot * E + kOutsideSlot * (double)out_count / n;
+            for (int h = 0; h <= max_shift; ++h) {
+                const double stretch = (double)max(run_l >> h, 1);
+                const double missed = E * (double)far_count[h] / n;
+                const double values = kLargeCost + kLargeSlot * E + kLargeBatch / stretch +
+                                      kOutsideSlot * missed;
+                const double jumps = kJumpCost + kJumpBatch / stretch + kOutsideJump * missed;
+                if (values < best) {
+                    best = values;
+                    choice = kRingSel64 + h;
+                }
+                if (jumps_ok && jumps < best) {
+                    best = jumps;
+                    choice = (kRingSel64 + h) | kRingSelJumps;
+                }
+            }
+        }
+        sel[tile] = (uint8_t)choice;
+    }
 }
 
 // M: arithmetic of the deposit (field in double or single; accumulation in
@@ -1158,28 +1342,24 @@ struct ModeTypes {
     using Rec = typename std::conditional<MIX, RecMix, RecF64>::type;  // staged state record
 };
 
-// Segments a workgroup of shape SH stages per batch: a whole run with the small
-// ring; with the large ring at most kLargeStage (a run of more is staged in
-// parts), because the arrivals of a batch must fit the ring's span.
-template <int R, int SH>
-constexpr int kSubRun =
-    (R == kRingLarge && shape_run(SH) > kLargeStage) ? kLargeStage : shape_run(SH);
-
 // LDS of one deposit workgroup of shape SH with rings of R slots
 template <int M, int R, int SH>
 struct DepositShared {
     using Acc = typename ModeTypes<M>::Acc;
     static constexpr int TC = shape_cells(SH);   // cells per tile
     static constexpr int GR = shape_groups(SH);  // particles per batch
-    // one cell's ring, padded by one word so that the rings of the tile's
-    // cells, which one instruction updates together, start in different banks
-    static constexpr int kStride = R * CellSink<Acc, R>::W + 1;
-    static constexpr int L = kSubRun<R, SH>;
-    static_assert(shape_run(SH) % L == 0, "a run is a whole number of staged parts");
+    // the rings' words, cell fastest: an update of several cells by one instruction
+    // meets no bank twice but for lanes of one cell
+    static constexpr int kRingWords = TC * R * 6;
+    static constexpr int L = shape_run(SH);
     typename ModeTypes<M>::Rec rec[GR][L + 1];  // staged batch: L segments per group
     double sq[GR];                      // its charges
     double tk[L + 1];                   // its states' time arguments (the same for every lane)
-    double ring[TC * kStride];          // per-cell slot rings
+    double ring[kRingWords];            // per-cell slot rings, [slot][component][cell]
+    // a ring of jumps: per cell and slot, runs starting there minus runs that ended before
+    static constexpr int kRunStride = R + 1;
+    int runs[R == kRingLarge && M != kModeF64 ? TC * kRunStride : 1];
+    int ring_base[TC];                  // per cell: where its ring starts
     int nb[2][TC];                      // per cell: lowest start slot of a coming batch
     int ord[2][GR];                     // particles of the staged rows, per batch parity
     unsigned long long cnt[kCounters];  // clipped, nonmonotone, bypassed, large-ring interactions
@@ -1199,9 +1379,11 @@ struct DepositShared {
 // DIV: the double slot coordinate divides (a divisor that fails the host check
 // of canon_slot's corrections); a compile-time choice, so that the state loop
 // carries no branch for it.
+// sel: the tile's ring choice (large ring: the stretches its runs are staged in,
+// and whether it holds jumps).
 template <int M, int R, int G, int HOLD, int SH, bool DIV>
 __device__ __forceinline__ void deposit_item(const DepositJob& J, int64_t tile, int64_t split,
-                                             int64_t part, DepositShared<M, R, SH>& sh)
+                                             int64_t part, int sel, DepositShared<M, R, SH>& sh)
 {
     constexpr int kTileCells = shape_cells(SH);  // this shape's tile, batch and run
     constexpr int kGroups = shape_groups(SH);
@@ -1211,9 +1393,11 @@ __device__ __forceinline__ void deposit_item(const DepositJob& J, int64_t tile, 
     constexpr bool MIX = ModeTypes<M>::MIX;
     using T = typename ModeTypes<M>::T;
     using Acc = typename ModeTypes<M>::Acc;
-    using Sink = CellSink<Acc, R>;
+    using Sink = CellSink<Acc, R, kTileCells>;
     using Rec = typename ModeTypes<M>::Rec;
     constexpr int RW = Sink::W;
+    constexpr bool kJumps = R == kRingLarge && jumps<M, HOLD>;  // the ring may hold jumps
+    const bool jump = kJumps && (sel & kRingSelJumps) != 0;
     const Rec* recs = reinterpret_cast<const Rec*>(J.recs);
 
     const int tid = threadIdx.x;
@@ -1258,14 +1442,19 @@ __device__ __forceinline__ void deposit_item(const DepositJob& J, int64_t tile, 
         else
             return MIX ? slot_coord_mixed(xc, st.x, tk, K) : slot_coord_fp64(xc, st.x, tk, K);
     };
-    RADIO_LDS double* my_ring = (RADIO_LDS double*)&sh.ring[cl * DepositShared<M, R, SH>::kStride];
+    RADIO_LDS double* my_ring = (RADIO_LDS double*)&sh.ring[cl];
     RADIO_LDS int* nb = (RADIO_LDS int*)&sh.nb[0][0];
     for (int i = g; i < R * RW; i += kGroups)
-        my_ring[i] = 0.0;
+        my_ring[i * kTileCells] = 0.0;
+    if constexpr (kJumps)
+        for (int i = tid; i < (int)(sizeof(sh.runs) / sizeof(int)); i += kDepositThreads)
+            sh.runs[i] = 0;
     if (tid < kCounters)
         sh.cnt[tid] = 0;
     if (tid < 2 * kTileCells)
         nb[tid] = INT_MAX;
+    if (tid < kTileCells)
+        sh.ring_base[tid] = 0;
     int base = 0;  // the ring covers [base, base + R), 0 <= base <= max(n_t - R, 0)
     unsigned n_clip = 0, n_back = 0, n_bypass = 0;
     unsigned n_large = 0;  // large ring: the lane's segments (its interactions)
@@ -1278,13 +1467,15 @@ __device__ __forceinline__ void deposit_item(const DepositJob& J, int64_t tile, 
     const int64_t bt_begin = part * J.batches_per_part;
     const int64_t bt_end = min(bt_begin + J.batches_per_part, (J.n_p + kGroups - 1) / kGroups);
     const int64_t n_batches = bt_end - bt_begin;  // per run
-    // The item's runs [rb_begin, rb_end), staged in parts of L segments: part
-    // rb (states rb * L ... rb * L + L) of run rb / NS.
-    constexpr int L = kSubRun<R, SH>;
-    constexpr int NS = kRunL / L;
-    const int64_t rb_begin = split * J.runs_per_split * NS;
+    // The item's runs [rb_begin, rb_end), staged in stretches of L segments: stretch
+    // rb (states rb * L ... rb * L + L) of run rb >> ns_shift.
+    // log2 of the stretches of a run
+    const int ns_shift = R == kRingLarge ? (sel & kRingSelShift) - kRingSel64 : 0;
+    const int L = kRunL >> ns_shift;
+    const int64_t rb_begin = (split * J.runs_per_split) << ns_shift;
     const int64_t rb_end =
-        min(min(split * J.runs_per_split + J.runs_per_split, J.n_runs) * NS, (J.n_s + L - 1) / L);
+        min(min(split * J.runs_per_split + J.runs_per_split, J.n_runs) << ns_shift,
+            (J.n_s + L - 1) / L);
     // The item's batches are taken part-major: part rb of the particles
     // order[bt * kGroups ...], bt = bt_begin .. bt_end - 1.
     // Before a batch is computed, one round of global loads brings its
@@ -1301,7 +1492,7 @@ __device__ __forceinline__ void deposit_item(const DepositJob& J, int64_t tile, 
     // the lane's particle of batch (rb_, bt_), or -1 (the order of the part's run)
     auto lane_particle = [&](int64_t rb_, int64_t bt_, int lane_g) -> int {
         const int64_t i = bt_ * kGroups + lane_g;
-        return (rb_ < rb_end && i < J.n_p) ? (int)order_of(rb_ / NS)[i] : -1;
+        return (rb_ < rb_end && i < J.n_p) ? (int)order_of(rb_ >> ns_shift)[i] : -1;
     };
     // lowest start slot of the cell over a batch: the lane's particle starts at x
     // at state s_a (into nb[buf][cell])
@@ -1327,42 +1518,91 @@ __device__ __forceinline__ void deposit_item(const DepositJob& J, int64_t tile, 
         return gptr(reinterpret_cast<const double*>(recs + (int64_t)p * n_states + s_a));
     };
 
-    // Move the ring to start at new_base: slots leaving it go to HBM.  The
-    // cell's kGroups lanes share the work.
-    auto move_ring = [&](int new_base) {
-        if (active) {
-            int lo = base, hi = base + R;  // slots to flush
-            if (new_base > base && new_base < base + R)
-                hi = new_base;
-            for (int j = lo + g; j < hi; j += kGroups) {
-                RADIO_LDS double* q = my_ring + ring_pos<R>(j) * RW;
-                double a[RW];
-                bool nz = false;
+    // where the ring of a cell starts for a batch whose lowest start slot is lo_slot
+    // (a ring of jumps ends segments, but holds none, in its last two slots)
+    auto placed = [&](int lo_slot, int cur) {
+        if (lo_slot == INT_MAX)
+            return cur;
+        return (int)fmin(fmax((double)lo_slot - (double)kRingMargin, 0.0),
+                         fmax((double)(n_t - R + (jump ? 2 : 0)), 0.0));
+    };
+    // Move the rings: slots leaving them go to HBM.  Eight lanes of one wavefront
+    // (six of them at work, one per component) take a cell's slot, so that its adds
+    // share a line; a ring of values gives kSubs slots to as many such groups.  In a
+    // ring of jumps one group walks the slots, four a round (what its lanes read of
+    // the run counts is read by one instruction, before any of them clears it): the
+    // running sum goes to the detector slot by slot, and on into the first slot that
+    // stays.
+    constexpr int kCellsPerWave = kTileCells / (kDepositThreads / 64);
+    constexpr int kSubs = 64 / (8 * kCellsPerWave);
+    static_assert(kCellsPerWave * 8 <= 64, "eight lanes of a wavefront per cell");
+    auto move_rings = [&](int buf, bool all) {
+        int t = tid;
+        asm volatile("" : "+v"(t));  // derived per batch, not held through the field loop
+        const int f_comp = t % 8;
+        const int f_sub = (t % 64) / (8 * kCellsPerWave);
+        const int f_cell = (t / 64) * kCellsPerWave + (t / 8) % kCellsPerWave;
+        const int64_t f_row_i = tile * kTileCells + f_cell;
+        const int f_base = sh.ring_base[f_cell];
+        const int new_base = all ? -1 : placed(nb[buf * kTileCells + f_cell], f_base);
+        if (new_base == f_base || f_comp >= 6 || f_row_i >= J.n_c)
+            return;
+        RADIO_LDS double* comp = (RADIO_LDS double*)&sh.ring[f_comp * kTileCells + f_cell];
+        RADIO_GLOBAL Acc* f_row = gptr(reinterpret_cast<Acc*>(J.acc + f_row_i * J.n_t * 6));
+        const bool part = new_base > f_base && new_base < f_base + R;
+        const int hi = part ? new_base : f_base + R;
+        if (!jump) {
+            for (int j0 = f_base + f_sub; j0 < hi; j0 += 4 * kSubs) {
+                double d[4];
 #pragma unroll
-                for (int k = 0; k < RW; ++k) {
-                    a[k] = q[k];
-                    q[k] = 0.0;
-                    nz |= (a[k] != 0.0);
+                for (int i = 0; i < 4; ++i) {
+                    RADIO_LDS double* q = comp + ring_pos<R>(j0 + i * kSubs) * (RW * kTileCells);
+                    d[i] = j0 + i * kSubs < hi ? *q : 0.0;
+                    if (d[i] != 0.0)
+                        *q = 0.0;
                 }
-                if (nz && j < n_t) {
-                    if constexpr (M == kModeMixTwoSum) {
-                        // the slot's double sum as a compensated pair
-                        float hi[6], lo[6];
 #pragma unroll
-                        for (int k = 0; k < 6; ++k) {
-                            hi[k] = (float)a[k];
-                            lo[k] = (float)(a[k] - (double)hi[k]);
-                        }
-                        global_add_pair(row, j, hi, lo);
-                    } else {
-                        global_add(row, j, a);
+                for (int i = 0; i < 4; ++i)
+                    if (d[i] != 0.0 && j0 + i * kSubs < n_t)
+                        global_add_one(f_row, j0 + i * kSubs, f_comp, d[i]);
+            }
+        } else if constexpr (kJumps) {
+            if (f_sub != 0)
+                return;
+            RADIO_LDS int* runs =
+                (RADIO_LDS int*)&sh.runs[f_cell * DepositShared<M, R, SH>::kRunStride];
+            double level = 0.0;
+            int open = 0;  // runs touching the slot
+            for (int j0 = f_base; j0 < hi; j0 += 4) {
+                double d[4];
+                int r[4];
+#pragma unroll
+                for (int i = 0; i < 4; ++i) {
+                    const int pos = ring_pos<R>(j0 + i);
+                    d[i] = comp[pos * (RW * kTileCells)];
+                    r[i] = runs[pos];
+                }
+#pragma unroll
+                for (int i = 0; i < 4; ++i)
+                    if (j0 + i < hi) {
+                        const int pos = ring_pos<R>(j0 + i);
+                        comp[pos * (RW * kTileCells)] = 0.0;
+                        runs[pos] = 0;
+                        open += r[i];
+                        level = open != 0 ? level + d[i] : 0.0;
+                        if (level != 0.0 && j0 + i < n_t)
+                            global_add_one(f_row, j0 + i, f_comp, level);
                     }
-                }
+            }
+            if (part && open != 0) {
+                comp[ring_pos<R>(new_base) * (RW * kTileCells)] += level;
+                if (f_comp == 0)
+                    runs[ring_pos<R>(new_base)] += open;
             }
         }
-        base = new_base;
+        if (f_comp == 0 && f_sub == 0)
+            sh.ring_base[f_cell] = new_base;
     };
-
     // Staging of a batch's records.  Single-precision kernels load them from
     // HBM straight into LDS (no registers held for them, which keeps their
     // register count at five wavefronts per SIMD); the double kernel, whose LDS
@@ -1385,7 +1625,7 @@ __device__ __forceinline__ void deposit_item(const DepositJob& J, int64_t tile, 
     // bytes where the record size allows, else of 8)
     using Piece = typename std::conditional<sizeof(Rec) % 16 == 0, v2i64, long long>::type;
     constexpr int kPieces = (int)(sizeof(Rec) / sizeof(Piece));
-    constexpr int kIter = ((L + 1) * kPieces + kStageLanes - 1) / kStageLanes;
+    constexpr int kIter = ((kRunL + 1) * kPieces + kStageLanes - 1) / kStageLanes;
     // the records (states s_a .. s_a + L, contiguous) and the charge of particle p
     auto load_records = [&](int p, int64_t s_a_, Piece(&v)[kIter], double& qs) {
         const int per = (int)(min((int64_t)L, J.n_s - s_a_) + 1) * kPieces;
@@ -1454,14 +1694,8 @@ __device__ __forceinline__ void deposit_item(const DepositJob& J, int64_t tile, 
         const int np = (int)min((int64_t)kGroups, J.n_p - i0);
         // slide the ring to this batch's earliest start (every lane of the
         // previous batch is past the barrier that ended it)
-        const int lo_slot = nb[buf * kTileCells + cl];
-        if (lo_slot != INT_MAX) {
-            const double mc = fmin(fmax((double)lo_slot - (double)kRingMargin, 0.0),
-                                   fmax((double)(n_t - R), 0.0));
-            const int nbase = (int)mc;
-            if (nbase != base)
-                move_ring(nbase);
-        }
+        move_rings(buf, false);
+        base = placed(nb[buf * kTileCells + cl], base);
         int64_t rb2 = rb1, bt2 = bt1;  // the batch after the next
         advance(rb2, bt2);
         if constexpr (kStageDirect) {
@@ -1475,7 +1709,7 @@ __device__ __forceinline__ void deposit_item(const DepositJob& J, int64_t tile, 
             // batch's first positions for the ring.
             static_assert(sizeof(Rec) % 16 == 0, "records move in 16-byte pieces");
             constexpr int kPieces = (int)(sizeof(Rec) / 16);
-            constexpr int kPer = (L + 1) * kPieces;  // pieces of a full row
+            constexpr int kPer = (kRunL + 1) * kPieces;  // pieces of a full row
             constexpr int kWaves = kDepositThreads / 64;
             constexpr int kRowsPerWave = kGroups / kWaves;
             constexpr int kHalves = (kPer + 63) / 64;  // rounds per row
@@ -1597,7 +1831,6 @@ __device__ __forceinline__ void deposit_item(const DepositJob& J, int64_t tile, 
         if (active && g < np) {
             if constexpr (R == kRingLarge)
                 n_large += (unsigned)len;
-            Sink sink{my_ring, row, base, n_t, &n_bypass};
             const double q = sh.sq[g];
             // (the mixed records carry q/c in their betadot)
             const T qc = T(q * J.inv_c), qv = T(q * J.vscale), qv2 = T(2.0 * q * J.vscale);
@@ -1624,47 +1857,109 @@ __device__ __forceinline__ void deposit_item(const DepositJob& J, int64_t tile, 
                 u_prev = field_at(sh.rec[g][0], sh.tk[0], Fp);
             else
                 u_prev = slot_of(sh.rec[g][0], sh.tk[0]);
-            Carry<T> C;
-            // open the slot where the run starts (a start far outside the window
-            // leaves the first segment to the general path)
-            const bool inside = u_prev >= -1.0 && u_prev < ntd + 1.0;
-            carry_open(C, inside ? floor(u_prev) : (double)(INT_MIN / 2));
-            C.lim = fast_limit(C.J1 - 1.0, u_prev, ntd);
-            // segment k: the field of state k, held (or interpolated) over its arrivals
-            auto segment = [&](const Rec& st, double tk) {
-                T F[6];
-                const double uk = field_at(st, tk, F);
-                if constexpr (HOLD == 0) {
-                    add_segment(C, sink, n_t, u_prev, uk, F, n_back, n_clip);
+            // states 1 .. len through segment(); with the large ring the next state's
+            // record is read from LDS while this one is worked on (two waves per SIMD
+            // hide little of the LDS latency)
+            auto walk = [&](auto&& segment) {
+                if constexpr (kPrefetch) {
+                    Rec cur = sh.rec[g][1];
+                    double t_cur = sh.tk[1];
+                    for (int k = 1; k <= len; ++k) {
+                        const int kn = min(k + 1, len);
+                        const Rec nxt = sh.rec[g][kn];
+                        const double t_nxt = sh.tk[kn];
+                        segment(cur, t_cur);
+                        cur = nxt;
+                        t_cur = t_nxt;
+                    }
                 } else {
-                    if constexpr (HOLD == 1)
-                        add_segment(C, sink, n_t, u_prev, uk, Fp, n_back, n_clip);
-                    else
-                        add_segment_linear(C, sink, n_t, u_prev, uk, Fp, F, n_back, n_clip);
-#pragma unroll
-                    for (int c = 0; c < 6; ++c)
-                        Fp[c] = F[c];
+                    for (int k = 1; k <= len; ++k)
+                        segment(sh.rec[g][k], sh.tk[k]);
                 }
-                u_prev = uk;
             };
-            if constexpr (kPrefetch) {
-                // the next state's record is read from LDS while this one is
-                // worked on (two waves per SIMD hide little of the LDS latency)
-                Rec cur = sh.rec[g][1];
-                double t_cur = sh.tk[1];
-                for (int k = 1; k <= len; ++k) {
-                    const int kn = min(k + 1, len);
-                    const Rec nxt = sh.rec[g][kn];
-                    const double t_nxt = sh.tk[kn];
-                    segment(cur, t_cur);
-                    cur = nxt;
-                    t_cur = t_nxt;
-                }
+            auto deposit_jumps = [&] {
+                const double wlo = (double)base;
+                const double whi = fmin((double)(base + R - 2), ntd);
+                double at = ring_clamp(u_prev, wlo, whi);  // where the next jump goes
+                double first = at, last = at;              // what the run touches
+                // bound of the fast path: the segment starts in the ring's span
+                double lim = (u_prev >= wlo && u_prev <= whi) ? whi : -INFINITY;
+                double held[6] = {0.0, 0.0, 0.0, 0.0, 0.0, 0.0};
+                walk([&](const Rec& st, double tk) {
+                    T F[6], H[6];
+                    const double uk = field_at(st, tk, F);
+#pragma unroll
+                    for (int c = 0; c < 6; ++c) {
+                        H[c] = HOLD == 1 ? Fp[c] : F[c];
+                        if constexpr (HOLD == 1)
+                            Fp[c] = F[c];
+                    }
+                    double next = uk;
+                    if (!((uk >= u_prev) & (uk <= lim) & ordinary(H, POT))) {
+                        jump_general(row, u_prev, uk, wlo, whi, n_t, POT, H, n_back, n_clip,
+                                     n_bypass);
+                        next = ring_clamp(uk, wlo, whi);
+                        first = fmin(first, next);
+                        last = fmax(last, fmax(at, next));
+                        lim = (uk >= wlo && uk <= whi) ? whi : -INFINITY;
+                    }
+                    double d[6];
+#pragma unroll
+                    for (int c = 0; c < 6; ++c) {
+                        const double h = (double)H[c];
+                        d[c] = h - held[c];
+                        held[c] = h;
+                    }
+                    add_jump<R, kTileCells>(my_ring, at, d);
+                    at = next;
+                    u_prev = uk;
+                });
+#pragma unroll
+                for (int c = 0; c < 6; ++c)
+                    held[c] = -held[c];
+                add_jump<R, kTileCells>(my_ring, at, held);
+                RADIO_LDS int* runs =
+                    (RADIO_LDS int*)&sh.runs[cl * DepositShared<M, R, SH>::kRunStride];
+                __hip_atomic_fetch_add(runs + ring_pos<R>((int)first), 1, __ATOMIC_RELAXED,
+                                       __HIP_MEMORY_SCOPE_WORKGROUP);
+                __hip_atomic_fetch_add(runs + ring_pos<R>((int)fmax(last, at) + 1), -1,
+                                       __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
+            };
+            auto deposit_values = [&] {
+                Sink sink{my_ring, row, base, n_t, &n_bypass};
+                Carry<T> C;
+                // open the slot where the run starts (a start far outside the window
+                // leaves the first segment to the general path)
+                const bool inside = u_prev >= -1.0 && u_prev < ntd + 1.0;
+                carry_open(C, inside ? floor(u_prev) : (double)(INT_MIN / 2));
+                C.lim = fast_limit(C.J1 - 1.0, u_prev, ntd);
+                // segment k: the field of state k, held (or interpolated) over its arrivals
+                walk([&](const Rec& st, double tk) {
+                    T F[6];
+                    const double uk = field_at(st, tk, F);
+                    if constexpr (HOLD == 0) {
+                        add_segment(C, sink, n_t, u_prev, uk, F, n_back, n_clip);
+                    } else {
+                        if constexpr (HOLD == 1)
+                            add_segment(C, sink, n_t, u_prev, uk, Fp, n_back, n_clip);
+                        else
+                            add_segment_linear(C, sink, n_t, u_prev, uk, Fp, F, n_back, n_clip);
+#pragma unroll
+                        for (int c = 0; c < 6; ++c)
+                            Fp[c] = F[c];
+                    }
+                    u_prev = uk;
+                });
+                sink.flush((int)(C.J1 - 1.0), C.V);
+            };
+            if constexpr (kJumps) {
+                if (jump)
+                    deposit_jumps();
+                else
+                    deposit_values();
             } else {
-                for (int k = 1; k <= len; ++k)
-                    segment(sh.rec[g][k], sh.tk[k]);
+                deposit_values();
             }
-            sink.flush((int)(C.J1 - 1.0), C.V);
         }
         if constexpr (kPrefetch) {
             if (scout_next)
@@ -1679,7 +1974,7 @@ __device__ __forceinline__ void deposit_item(const DepositJob& J, int64_t tile, 
         rb1 = rb2;
         bt1 = bt2;
     }
-    move_ring(-1);  // flush what the ring still holds
+    move_rings(0, true);  // flush what the rings still hold
     if (n_clip)
         atomicAdd(&sh.cnt[0], (unsigned long long)n_clip);
     if (n_back)
@@ -1698,15 +1993,16 @@ __device__ __forceinline__ void deposit_item(const DepositJob& J, int64_t tile, 
 // modes have one)
 template <int M, int R, int G, int HOLD, int SH>
 __device__ __forceinline__ void deposit_item_of(const DepositJob& J, int64_t tile, int64_t split,
-                                                int64_t part, DepositShared<M, R, SH>& sh)
+                                                int64_t part, int sel,
+                                                DepositShared<M, R, SH>& sh)
 {
     if constexpr (M == kModeF64) {
         if (J.slot_div)
-            deposit_item<M, R, G, HOLD, SH, true>(J, tile, split, part, sh);
+            deposit_item<M, R, G, HOLD, SH, true>(J, tile, split, part, sel, sh);
         else
-            deposit_item<M, R, G, HOLD, SH, false>(J, tile, split, part, sh);
+            deposit_item<M, R, G, HOLD, SH, false>(J, tile, split, part, sel, sh);
     } else {
-        deposit_item<M, R, G, HOLD, SH, false>(J, tile, split, part, sh);
+        deposit_item<M, R, G, HOLD, SH, false>(J, tile, split, part, sel, sh);
     }
 }
 
@@ -1751,10 +2047,11 @@ __attribute__((amdgpu_waves_per_eu(kMinWaves<M, R, G, HOLD, SH>))) void deposit_
     if (logical >= J.n_tiles * J.n_splits * J.n_parts)
         return;
     const int64_t tile = logical % J.n_tiles;
-    if (gptr(J.ring_sel)[tile] != (R == kRingLarge ? 1 : 0))
+    const int sel = gptr(J.ring_sel)[tile];
+    if ((sel != kRingSel16) != (R == kRingLarge))
         return;
     const int64_t rest = logical / J.n_tiles;  // split-major, then part
-    deposit_item_of<M, R, G, HOLD, SH>(J, tile, rest / J.n_parts, rest % J.n_parts, sh);
+    deposit_item_of<M, R, G, HOLD, SH>(J, tile, rest / J.n_parts, rest % J.n_parts, sel, sh);
 }
 
 // Persistent workgroups for many independent deposits: each takes the next work
@@ -1791,9 +2088,10 @@ deposit_persistent_kernel(
             break;
         const WorkItem w = items[it];
         const DepositJob J = jobs[w.job];
-        if (gptr(J.ring_sel)[w.tile] != (R == kRingLarge ? 1 : 0))
+        const int sel = gptr(J.ring_sel)[w.tile];
+        if ((sel != kRingSel16) != (R == kRingLarge))
             continue;
-        deposit_item_of<M, R, G, HOLD, SH>(J, w.tile, w.split, w.part, sh);
+        deposit_item_of<M, R, G, HOLD, SH>(J, w.tile, w.split, w.part, sel, sh);
     }
 }
 
@@ -2009,13 +2307,17 @@ hipError_t launch_ring_choice(const DepositJob& job, int mode, hipStream_t s)
 {
     if (job.n_tiles <= 0)
         return hipSuccess;
+    int max_shift = 0;  // stretches down to one segment
+    while (max_shift < kMaxPartShift && (job.run_l >> (max_shift + 1)) > 0)
+        ++max_shift;
     hipLaunchKernelGGL(ring_choice_kernel, dim3((unsigned)job.n_tiles), dim3(256), 0, s,
                        reinterpret_cast<const char*>(job.recs), (int64_t)rec_bytes(mode),
                        job.perm, job.n_tiles, job.runs_per_group, job.cells, job.far, job.n_c,
                        job.n_p, job.n_s, job.n_runs,
                        job.t_first,
                        job.s0, job.dt, job.t0, job.inv_dt_det, job.inv_c, job.n_t,
-                       (int)job.tile_cells, (int)job.groups, (int)job.run_l, job.ring_sel);
+                       (int)job.tile_cells, (int)job.groups, (int)job.run_l, max_shift,
+                       (mode != kModeF64 && job.hold != 2) ? 1 : 0, job.ring_sel);
     return hipGetLastError();
 }
 
