@@ -2095,6 +2095,156 @@ deposit_persistent_kernel(
     }
 }
 
+// ---------------------------------------------------------------------------
+// few particles
+// ---------------------------------------------------------------------------
+
+// A chunk of a few particles leaves the particle lanes of deposit_kernel idle, and
+// its four launches cost more than the work.  Here the lanes of a wavefront take
+// consecutive states of one particle: lane l > 0 the segment from lane l - 1's
+// state to its own, so that a state is evaluated once and its neighbour's arrival
+// and beta come by a shuffle.  A wavefront keeps its states' kinematics (formed
+// here, as kinematics_kernel forms them) in registers over kFewCells cells and all
+// of the chunk's particles; for each cell its lanes add their slots into an LDS window of
+// kFewWindow slots, which then goes to the detector as contiguous adds (2.5e10
+// slots/s against 3.8e9 for a lane adding a slot's six words).  One launch, no
+// workspace.  Bound by the latency of a wavefront's chain (field, LDS adds, flush) and,
+// with several slots a segment, by the adds to HBM.  Measured, whole deposits: one
+// electron x 2000 steps x 32 x 32 cells x 512 slots 163 -> 35 us, 25133 steps x 256
+// cells x 65536 slots 1.3 -> 0.55 ms.
+constexpr int kFewWindow = 192;  // slots; 64 segments of up to three slots, four workgroups a CU
+
+template <int M, bool DIV>
+__global__ __launch_bounds__(256) void few_kernel(DepositJob J, int64_t n_slabs, int64_t n_groups,
+                                                  int cells_each)
+{
+    constexpr bool MIX = ModeTypes<M>::MIX;
+    using T = typename ModeTypes<M>::T;
+    using Acc = typename ModeTypes<M>::Acc;
+    using Rec = typename ModeTypes<M>::Rec;
+    __shared__ double window[4][kFewWindow * 6];
+    const int lane = threadIdx.x % 64;
+    const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x / 64);
+    RADIO_LDS double* win = (RADIO_LDS double*)&window[wave][0];
+    for (int i = lane; i < kFewWindow * 6; i += 64)
+        win[i] = 0.0;
+    const double ntd = (double)J.n_t;
+    const Consts K{J.t0, J.inv_dt_det, J.inv_c, J.inv_c * J.inv_dt_det, J.dt_det, DIV};
+    unsigned long long n_clip = 0, n_back = 0;  // of the wavefront
+    for (int64_t task = (int64_t)blockIdx.x * 4 + wave; task < n_slabs * n_groups;
+         task += (int64_t)gridDim.x * 4) {
+        const int64_t slab = task / n_groups;
+        const int64_t c_begin = (task - slab * n_groups) * cells_each;
+        const int64_t c_end = min(c_begin + cells_each, J.n_c);
+        const int64_t s = slab * 63 + lane;  // the lane's state
+        const bool state = s <= J.n_s;
+        const bool segment = state && lane > 0;
+        const double sk = (double)(J.s0 + s);
+        double tk;  // the field functions' time argument
+        if constexpr (MIX)
+            tk = fma(sk, J.dt * J.inv_dt_det, (J.t_first - J.t0) * J.inv_dt_det);
+        else
+            tk = canon_state_time(J.t_first, sk, J.dt);
+        for (int64_t p = 0; p < J.n_p; ++p) {
+            const int64_t off = (state ? s : J.n_s) * J.n_p + p;
+            Rec st;
+            double b[3], g2i;
+    #pragma unroll
+            for (int c = 0; c < 3; ++c)
+                st.x[c] = gptr(J.x)[off + c * J.xs_stride];
+            canon_kinematics(gptr(J.u)[off], gptr(J.u)[off + J.xs_stride],
+                             gptr(J.u)[off + 2 * J.xs_stride], b, &g2i);
+            const double q = J.q ? gptr(J.q)[p] : -1.0;
+    #pragma unroll
+            for (int c = 0; c < 3; ++c) {
+                st.b[c] = b[c];
+                const double bd = canon_betadot(b[c], __shfl_up(b[c], 1), J.dt);
+                if constexpr (MIX)
+                    st.bdq[c] = (float)((q * J.inv_c) * bd);
+                else
+                    st.bd[c] = bd;
+            }
+            if constexpr (MIX)
+                st.g2ih = (float)(0.5 * g2i);
+            else
+                st.g2i = g2i;
+            for (int64_t cell = c_begin; cell < c_end; ++cell) {
+                const double* cp = J.cells + 3 * cell;
+                const double xc[3] = {cp[0], cp[1], cp[2]};
+                T F[6];
+                double u;
+                if constexpr (MIX)
+                    u = field_mixed(xc, st, tk, T(2.0 * q * J.vscale), K, F);
+                else
+                    u = field_fp64(xc, st, tk, T(q * J.inv_c), T(q * J.vscale), K, F);
+                const double a = __shfl_up(u, 1);
+                double lo = 0.0, hi = 0.0;
+                clamp_segment(a, u, ntd, lo, hi);
+                const bool adds = segment && lo < hi;  // else empty, entirely outside, or NaN
+                n_back += (unsigned)__popcll(__ballot(segment && u < a));
+                n_clip += (unsigned)__popcll(__ballot(segment && clipped(a, u, ntd) != 0u));
+                int j = adds ? (int)lo : INT_MAX;
+                const int j_end = adds ? (int)ceil(hi) : -1;  // past the last slot touched
+                // the slots the wavefront touches: as the arrivals advance with the lanes,
+                // from the first lane's to the last one's (else the extremes)
+                const unsigned long long on = __ballot(adds);
+                if (on == 0)
+                    continue;
+                int w_lo = __builtin_amdgcn_readlane(j, __builtin_ctzll(on));
+                int w_hi = __builtin_amdgcn_readlane(j_end, 63 - __builtin_clzll(on));
+                if (__ballot(adds && (j < w_lo || j_end > w_hi)) != 0) {
+                    w_lo = j;
+                    w_hi = j_end;
+                    for (int m = 32; m > 0; m >>= 1) {
+                        w_lo = min(w_lo, __shfl_xor(w_lo, m));
+                        w_hi = max(w_hi, __shfl_xor(w_hi, m));
+                    }
+                    w_lo = __builtin_amdgcn_readfirstlane(w_lo);
+                    w_hi = __builtin_amdgcn_readfirstlane(w_hi);
+                }
+                // few slots: as many copies of them as fit (at most 16), one per lane in
+                // turn, so that the lanes of one slot do not queue at one address
+                const int words = min(w_hi - w_lo, kFewWindow) * 6;
+                int copies = 1;
+                while (copies < 16 && 2 * copies * (words + 1) <= kFewWindow * 6)
+                    copies *= 2;
+                RADIO_LDS double* mine = win + (lane & (copies - 1)) * (words + 1);
+                RADIO_GLOBAL Acc* row = gptr(reinterpret_cast<Acc*>(J.acc + cell * J.n_t * 6));
+                for (int w0 = w_lo; w0 < w_hi; w0 += kFewWindow) {
+                    const int w1 = min(w0 + kFewWindow, w_hi);
+                    for (; j < min(j_end, w1); ++j) {
+                        const double jd = (double)j;
+                        const T wt = T(fmin(hi, jd + 1.0) - fmax(lo, jd));
+                        RADIO_LDS double* slot = mine + (j - w0) * 6;
+    #pragma unroll
+                        for (int k = 0; k < 6; ++k)
+                            __hip_atomic_fetch_add(slot + k, (double)(F[k] * wt), __ATOMIC_RELAXED,
+                                                   __HIP_MEMORY_SCOPE_WORKGROUP);
+                    }
+                    // the window is this wavefront's: its LDS accesses are done in order
+                    __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+                    for (int i = lane; i < (w1 - w0) * 6; i += 64) {
+                        double v = 0.0;
+                        for (int c = 0; c < copies; ++c) {
+                            v += win[c * (words + 1) + i];
+                            win[c * (words + 1) + i] = 0.0;
+                        }
+                        if (v != 0.0)
+                            global_add_one(row, w0 + i / 6, i % 6, v);
+                    }
+                    __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+                }
+            }
+        }
+    }
+    if (lane == 0 && n_clip)
+        __hip_atomic_fetch_add(gptr(J.counters), n_clip, __ATOMIC_RELAXED,
+                               __HIP_MEMORY_SCOPE_AGENT);
+    if (lane == 0 && n_back)
+        __hip_atomic_fetch_add(gptr(J.counters) + 1, n_back, __ATOMIC_RELAXED,
+                               __HIP_MEMORY_SCOPE_AGENT);
+}
+
 // E and B from the slot accumulator: E[c][j][0..2] and B[c][j][0..2] for the
 // caller's cell index c of internal row r.  The compensated single
 // accumulator holds (hi, lo) pairs, folded to double.  One thread per slot.
@@ -2406,6 +2556,35 @@ hipError_t launch_deposit(const DepositJob& job, int mode, int64_t max_grid, hip
     if (v < 0 || v >= kKernelVariants)
         return hipErrorInvalidValue;
     Variants::single[v](job, dim3((unsigned)blocks), s);
+    return hipGetLastError();
+}
+
+bool few_particles(const DepositJob& job)
+{
+    return job.n_p <= kFewParticles && job.hold == 0 && !job.potentials && !job.far;
+}
+
+hipError_t launch_few(const DepositJob& job, int mode, int64_t n_cus, hipStream_t s)
+{
+    const int64_t n_slabs = (job.n_s + 62) / 63;
+    // cells a wavefront takes: while sixteen wavefronts a CU remain
+    const int64_t each =
+        std::max<int64_t>(1, std::min<int64_t>(kFewCells, n_slabs * job.n_c / (16 * n_cus)));
+    const int64_t n_groups = (job.n_c + each - 1) / each;
+    const dim3 grid(
+        (unsigned)std::min<int64_t>((n_slabs * n_groups + 3) / 4, kMaxDepositGrid));
+    if (mode == kModeF64 && job.slot_div)
+        hipLaunchKernelGGL((few_kernel<kModeF64, true>), grid, dim3(256), 0, s, job, n_slabs,
+                           n_groups, (int)each);
+    else if (mode == kModeF64)
+        hipLaunchKernelGGL((few_kernel<kModeF64, false>), grid, dim3(256), 0, s, job, n_slabs,
+                           n_groups, (int)each);
+    else if (mode == kModeMix)
+        hipLaunchKernelGGL((few_kernel<kModeMix, false>), grid, dim3(256), 0, s, job, n_slabs,
+                           n_groups, (int)each);
+    else
+        hipLaunchKernelGGL((few_kernel<kModeMixTwoSum, false>), grid, dim3(256), 0, s, job,
+                           n_slabs, n_groups, (int)each);
     return hipGetLastError();
 }
 

@@ -444,6 +444,15 @@ int reserve(radio_detector* det, const radio::DepositJob& J, hipStream_t s)
 // Enqueue a deposit in its time slices.  Only the first (largest) slice can
 // grow the workspaces, so a later one cannot fail for memory after earlier
 // ones were enqueued.
+int enqueue_few(radio_detector* det, const radio::DepositJob& J, hipStream_t s)
+{
+    if (radio::launch_few(J, det->precision, det->n_cus, s) != hipSuccess)
+        return RADIO_EDEVICE;
+    det->slices += 1;
+    det->interactions += J.n_p * J.n_s * J.n_c;
+    return RADIO_OK;
+}
+
 int enqueue_deposit(radio_detector* det, const radio_chunk* k, hipStream_t s)
 {
     if (k->n_particles == 0 || k->n_steps == 0)
@@ -451,6 +460,8 @@ int enqueue_deposit(radio_detector* det, const radio_chunk* k, hipStream_t s)
     if (k->n_particles > INT32_MAX || k->n_steps > INT32_MAX - 1)
         return RADIO_EINVAL;
     const SlicePlan P = plan_slices(det, k);
+    if (radio::few_particles(P.W))
+        return enqueue_few(det, P.W, s);
     for (int64_t r_a = 0; r_a < P.W.n_runs; r_a += P.runs_each) {
         radio::DepositJob J = plan_slice(det, P, r_a);
         const int rc = reserve(det, J, s);
@@ -534,6 +545,8 @@ int enqueue_deposit_noalloc(radio_detector* det, const radio_chunk* k, hipStream
     const radio::DepositJob W = make_job(det, k);
     if (slice_scratch_bytes(W, det->precision, 1) > kScratchBytes)
         return RADIO_ETOOBIG;
+    if (radio::few_particles(W))
+        return enqueue_few(det, W, s);
     // the longest time slices that fit the scratch
     int64_t lo = 1, hi = W.n_runs;
     while (lo < hi) {
@@ -630,7 +643,7 @@ int enqueue_batch(radio_detector* const* dets, const radio_chunk* chunks, int n,
     // here, before anything is enqueued, so that a memory error leaves every
     // detector as it was.
     const radio_tuning tun = current_tuning();
-    std::vector<int> idx, sliced;
+    std::vector<int> idx, sliced;  // sliced: also the chunks of few particles
     size_t recs_need = 0, perm_need = 0, sel_need = 0;
     A->h_jobs.clear();
     for (int i = 0; i < n; ++i) {
@@ -638,6 +651,10 @@ int enqueue_batch(radio_detector* const* dets, const radio_chunk* chunks, int n,
         if (k->n_particles == 0 || k->n_steps == 0)
             continue;
         const SlicePlan P = plan_slices(dets[i], k);
+        if (radio::few_particles(P.W)) {  // one launch, no workspace
+            sliced.push_back(i);
+            continue;
+        }
         if (P.n_slices > 1) {
             const int rc = reserve(dets[i], plan_slice(dets[i], P, 0), s);
             if (rc != RADIO_OK)
