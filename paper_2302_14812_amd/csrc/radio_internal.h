@@ -235,7 +235,12 @@ hipError_t launch_spectrum_group(const double* acc, bool pairs, int64_t n_t, int
                                  const int64_t* user_index, const double* weights, double dt,
                                  double c, double2* work0, double2* work1, double2* tables,
                                  double* d2I, double* dIdw, double* dIdO, bool* parseval_done,
-                                 bool first_group, hipStream_t s);
+                                 bool first_group, int64_t n_cus, hipStream_t s);
+// Transforms up to this length take all cells at once (r0 = 0, G = n_c), with at
+// most kSpecParts workgroups, whose parts of dI/domega (N/2 + 1 doubles each) are in
+// work0.
+constexpr int64_t kSpecOneLaunch = 2048;
+constexpr int64_t kSpecParts = 1024;
 hipError_t launch_spectrum_parseval(const double* acc, bool pairs, int64_t n_c, int64_t n_t,
                                     const double* cells, const int64_t* user_index, double dt,
                                     double c, double* dIdO, hipStream_t s);

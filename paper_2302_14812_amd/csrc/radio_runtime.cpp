@@ -1210,16 +1210,20 @@ int radio_spectrum(radio_detector* det, int64_t n_fft, const double* weights, do
     const bool pairs = det->precision == RADIO_MIXED_TWOSUM;
     // cells per group: two complex work arrays of 2 G N values within ~1 GiB
     const int64_t per_cell = 2 * 2 * N * (int64_t)sizeof(double2);
-    const int64_t G = std::max<int64_t>(1, std::min<int64_t>(det->n_c, ((int64_t)1 << 30) / per_cell));
+    const bool one = N <= radio::kSpecOneLaunch;  // all cells at once, sums for work arrays
+    const int64_t G =
+        one ? det->n_c
+            : std::max<int64_t>(1, std::min<int64_t>(det->n_c, ((int64_t)1 << 30) / per_cell));
+    const int64_t work = one ? radio::kSpecParts * (N / 4 + 1) : 4 * G * N;  // complex values
     double2* w0 = nullptr;
     double2* w1 = nullptr;
     double* d_w = nullptr;
     int rc = RADIO_OK;
     if (d2I || dIdw) {
         // the two work arrays, kept by the detector for later spectra
-        rc = grow(&det->d_spec, &det->spec_cap, (size_t)(4 * G * N + radio::kSpecTableValues), s);
+        rc = grow(&det->d_spec, &det->spec_cap, (size_t)(work + radio::kSpecTableValues), s);
         w0 = det->d_spec;
-        w1 = det->d_spec + 2 * G * N;
+        w1 = det->d_spec + work / 2;
     }
     if (rc == RADIO_OK && weights && dIdw) {
         if (hipMalloc((void**)&d_w, (size_t)det->n_c * sizeof(double)) != hipSuccess) {
@@ -1238,8 +1242,8 @@ int radio_spectrum(radio_detector* det, int64_t n_fft, const double* weights, do
             bool done = false;
             if (radio::launch_spectrum_group(det->d_acc, pairs, det->n_t, r0, Gi, N, det->d_cells,
                                              det->d_user_index, d_w, det->dt_det, det->c, w0, w1,
-                                             det->d_spec + 4 * G * N, d2I, dIdw, dIdO, &done,
-                                             r0 == 0, s) != hipSuccess)
+                                             det->d_spec + work, d2I, dIdw, dIdO, &done, r0 == 0,
+                                             det->n_cus, s) != hipSuccess)
                 rc = RADIO_EDEVICE;
             parseval_done = parseval_done && done;
         }

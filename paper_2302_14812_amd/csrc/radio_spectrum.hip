@@ -24,12 +24,11 @@
 //                      cell in one tile, so that each slot is read once;
 //   spec_rows_kernel   the second step: tiles of rows (fixed k1, contiguous)
 //                      transformed in LDS and stored at k1 + N1 k2, the
-//                      spectrum in natural order; spec_rows_q_kernel
+//                      spectrum in natural order; spec_rows_q32_kernel
 //                      transforms the rows of both signals of a cell together
 //                      and stores only Q, row-major (8 bytes a frequency
 //                      instead of 32);
-//                      For N <= kFftTile the first step alone is the transform
-//                      (N2 = 1);
+//   spec_small_kernel  for N <= kFftTile: all of it in one pass, cell by cell;
 //   spec_load_kernel + spec_fft_pass   for N > kFftTile^2: packing, then
 //                      log2(N) radix-2 Stockham passes between two buffers;
 //   spec_power_kernel  a thread per frequency and block of cells: the power
@@ -90,6 +89,7 @@ __device__ __forceinline__ double2 cmul(double2 a, double2 b)
 constexpr int kTabLo = kFftTile / 2;
 constexpr int kTabHi = kTabLo + kFftTile;
 static_assert(kTabHi + kFftTile <= kSpecTableValues, "twiddle table layout");
+static_assert(kSpecOneLaunch == kFftTile, "one launch for what fits a tile");
 
 __global__ __launch_bounds__(256) void spec_tables_kernel(double2* __restrict__ tab, int lg)
 {
@@ -225,9 +225,9 @@ __global__ __launch_bounds__(kFftThreads) void spec_cols_kernel(const double* __
             continue;
         const int64_t sg = c >> lg2;
         const int64_t n2 = c & (N2 - 1);
-        double2 v = buf[t * N1 + k1];
-        if (lg2 > 0)  // exp(-2 pi i n2 k1 / N), argument reduced exactly
-            v = cmul(v, twiddle(tab, (n2 * (int64_t)k1) & (N - 1), lgS));
+        // exp(-2 pi i n2 k1 / N), argument reduced exactly
+        const double2 v =
+            cmul(buf[t * N1 + k1], twiddle(tab, (n2 * (int64_t)k1) & (N - 1), lgS));
         Y[sg * N + N2 * k1 + n2] = v;
     }
 }
@@ -335,46 +335,6 @@ __global__ __launch_bounds__(kFftThreads) void spec_cols2_kernel(const double* _
     }
 }
 
-// Second step for both signals of cell g, folding the two transforms into Q:
-// tile = Rh rows k1 of each signal (Rh = kFftTile / (2 N2), so lg2 <
-// kFftTileLg; N1 is a multiple of Rh), buf[s][r][N2].  Q is stored row-major,
-// Qt[g][k1 N2 + k2] = |Z1|^2 + |Z2|^2 at frequency k1 + N1 k2, so that the
-// stores are contiguous; spec_power_t_kernel transposes it.
-__global__ __launch_bounds__(kFftThreads) void spec_rows_q_kernel(const double2* __restrict__ Y,
-                                                                   int64_t G, int lg1, int lg2,
-                                                                   const double2* __restrict__ tab,
-                                                                   double* __restrict__ Q)
-{
-    extern __shared__ double2 lds[];
-    const int64_t N1 = (int64_t)1 << lg1;
-    const int N2 = 1 << lg2;
-    const int64_t N = N1 * N2;
-    const int lgH = kFftTileLg - 1 - lg2;
-    const int Rh = 1 << lgH;
-    double2* buf = lds;
-    double2* tw = lds + 2 * Rh * N2;
-    const int64_t tiles_per_cell = N1 >> lgH;
-    const int64_t g = blockIdx.x / tiles_per_cell;
-    const int64_t k10 = (blockIdx.x - g * tiles_per_cell) << lgH;
-    if (g >= G)
-        return;
-    fill_twiddles(tw, tab, lg2);
-    const double2* y = Y + (2 * g) * N + N2 * k10;  // Rh contiguous rows of signal 0
-    for (int e = threadIdx.x; e < Rh * N2; e += blockDim.x) {
-        const int r = e >> lg2;
-        const int j = bitrev(e & (N2 - 1), lg2);
-        buf[r * N2 + j] = y[e];
-        buf[(Rh + r) * N2 + j] = y[N + e];
-    }
-    lds_fft(buf, tw, lg2, 2 * Rh);
-    double* q = Q + g * N + N2 * k10;  // Rh contiguous rows
-    for (int e = threadIdx.x; e < Rh * N2; e += blockDim.x) {
-        const double2 a = buf[e];
-        const double2 b = buf[Rh * N2 + e];
-        q[e] = (a.x * a.x + a.y * a.y) + (b.x * b.x + b.y * b.y);
-    }
-}
-
 // In-register radix-2 transform (decimation in time) of 2^LG values loaded in
 // bit-reversed order, leaving them in natural order.  W[j] = exp(-2 pi i j /
 // 2^LG), j < 2^(LG-1), read with uniform addresses (scalar loads: the same
@@ -409,7 +369,8 @@ constexpr int kRow32 = 32;  // N2 = 1024 = 32 x 32
 // transforms over a in registers, multiplies by W_1024^(b c) and writes the 32
 // values to LDS; lane c then reads A[b][c] (b = 0 .. 31) and transforms over b.
 // Q = |Z1|^2 + |Z2|^2 is folded through LDS and stored row-major at
-// Qt[g][1024 k1 + c + 32 d], as spec_rows_q_kernel stores it.
+// Qt[g][1024 k1 + c + 32 d] at frequency k1 + N1 (c + 32 d), so that the stores are
+// contiguous; spec_power_t_kernel transposes it.
 __global__ __launch_bounds__(64) void spec_rows_q32_kernel(const double2* __restrict__ Y,
                                                            int64_t G, int lg1,
                                                            const double2* __restrict__ tab,
@@ -463,6 +424,227 @@ __global__ __launch_bounds__(64) void spec_rows_q32_kernel(const double2* __rest
 #pragma unroll
         for (int d = 0; d < kRow32; ++d)
             q[b + kRow32 * d] = (v[d].x * v[d].x + v[d].y * v[d].y) + P[d * (kRow32 + 1) + b];
+    }
+}
+
+// ---------------------------------------------------------------------------
+// transforms of up to kFftTile slots
+// ---------------------------------------------------------------------------
+
+// The whole spectrum of C = min(kFftTile / N, 64) cells at a time in one kernel:
+// a slot is read once (from the detector's E beside B: 48 bytes for 24), its
+// |E|^2 summed for dI/dOmega, both signals transformed in LDS, and the power
+// stored and added up over the workgroup's cells.  Persistent workgroups, two a CU:
+// a thread keeps its output frequencies, their slot weights and their part of
+// dI/domega in registers over all cells, and has the next cells' slots in flight
+// while it transforms.  Bound by the LDS passes and by HBM reading the detector
+// (2.9 TB/s).  Measured against columns, power and a separate Parseval pass, which
+// wrote and read both signals' spectra between them: 16384 cells x 2048 slots with
+// weights 1.35 -> 0.56 ms a call, 4000 cells x 300 slots 94 -> 74 us, 37 x 37 41 -> 40.
+constexpr int kSmallCells = 64;                       // cells at a time, at most
+constexpr int kSmallThreads = 512;                    // four wavefronts a SIMD
+constexpr int kSmallPer = kFftTile / kSmallThreads;   // slots, and outputs, of a thread
+
+// Position of value i of a transform of 2^lg in LDS.  Sixteen values span the
+// banks, and sixteen consecutive threads reach a pass's values at strides of 4 or 16
+// (bits 4 and 5 of the index) or store them in bit-reversed order (the four highest
+// bits): these bits are folded into the lowest four, so that each of these meets
+// every bank once.
+__device__ __forceinline__ int lds_at(int i, int lg)
+{
+    const int s = (i >> 4) & 3;
+    return i ^ s ^ (s << 2) ^ ((i >> max(5, lg - 4)) & 15);
+}
+
+// lds_fft on values kept at lds_at(); tw holds the first quarter of the circle, all
+// that two stages per pass read.
+__device__ __forceinline__ void lds_fft_at(double2* buf, const double2* tw, int lg, int T)
+{
+    const int len = 1 << lg;
+    int lgh = 0;
+    if (lg & 1) {
+        __syncthreads();
+        for (int b = threadIdx.x; b < T * (len >> 1); b += kSmallThreads) {
+            double2* x = buf + lds_at(2 * b, lg);
+            double2* y = buf + lds_at(2 * b + 1, lg);
+            const double2 a = *x, c = *y;
+            *x = make_double2(a.x + c.x, a.y + c.y);
+            *y = make_double2(a.x - c.x, a.y - c.y);
+        }
+        lgh = 1;
+    }
+    for (; lgh + 2 <= lg; lgh += 2) {
+        __syncthreads();
+        const int h = 1 << lgh;
+        const int step = len >> (lgh + 2);  // W_4h^k = tw[k step]
+#pragma unroll 1
+        for (int b = threadIdx.x; b < T * (len >> 2); b += kSmallThreads) {
+            const int k = b & (h - 1);
+            const int i = ((b >> lgh) << (lgh + 2)) + k;
+            double2* x0 = buf + lds_at(i, lg);
+            double2* x1 = buf + lds_at(i + h, lg);
+            double2* x2 = buf + lds_at(i + 2 * h, lg);
+            double2* x3 = buf + lds_at(i + 3 * h, lg);
+            const double2 a0 = *x0, a1 = *x1, a2 = *x2, a3 = *x3;
+            const double2 w2 = tw[k * step];
+            const double2 w1 = cmul(w2, w2);
+            const double2 w3 = make_double2(w2.y, -w2.x);
+            const double2 t1 = cmul(a1, w1), t3 = cmul(a3, w1);
+            const double2 b0 = make_double2(a0.x + t1.x, a0.y + t1.y);
+            const double2 b1 = make_double2(a0.x - t1.x, a0.y - t1.y);
+            const double2 b2 = make_double2(a2.x + t3.x, a2.y + t3.y);
+            const double2 b3 = make_double2(a2.x - t3.x, a2.y - t3.y);
+            const double2 t2 = cmul(b2, w2), t4 = cmul(b3, w3);
+            *x0 = make_double2(b0.x + t2.x, b0.y + t2.y);
+            *x2 = make_double2(b0.x - t2.x, b0.y - t2.y);
+            *x1 = make_double2(b1.x + t4.x, b1.y + t4.y);
+            *x3 = make_double2(b1.x - t4.x, b1.y - t4.y);
+        }
+    }
+    __syncthreads();
+}
+
+template <bool PAIRS>
+__global__ __launch_bounds__(kSmallThreads, 4) void spec_small_kernel(
+    const double* __restrict__ acc, int64_t n_t, int64_t n_c, int lg,
+    const double2* __restrict__ tab, const double* __restrict__ cells,
+    const int64_t* __restrict__ user_index, const double* __restrict__ weights, double dt, double c,
+    double* __restrict__ d2I, double* __restrict__ sums, double* __restrict__ dIdO)
+{
+    __shared__ double2 buf[2 * kFftTile];  // [signal][cell][slot], at lds_at()
+    __shared__ double2 tw[kFftTile / 4];
+    __shared__ double part[kSmallCells];   // sums of |E|^2
+    const int tid = threadIdx.x;
+    const int N = 1 << lg;
+    const int lgC = min(kFftTileLg - lg, 6);
+    const int C = 1 << lgC;
+    const int total = C << lg;             // slots at a time (at most kFftTile)
+    const int n_f = N / 2 + 1;
+    for (int k = tid; k < N / 4; k += kSmallThreads)
+        tw[k] = tab[k << (kFftTileLg - lg)];
+    if (tid < kSmallCells)
+        part[tid] = 0.0;
+    // the thread's outputs: cell of the tile, frequency, |(e^{-i w dt} - 1)/(-i w)|^2
+    int oc[kSmallPer], om[kSmallPer];
+    double W2[kSmallPer], sum[kSmallPer];
+#pragma unroll
+    for (int i = 0; i < kSmallPer; ++i) {
+        const int o = tid + kSmallThreads * i;
+        oc[i] = o < C * n_f ? o / n_f : -1;
+        om[i] = o - (o / n_f) * n_f;
+        const double omega = 2.0 * kPi * (double)om[i] / ((double)N * dt);
+        const double sw = om[i] == 0 ? dt : 2.0 * sin(0.5 * omega * dt) / omega;
+        W2[i] = sw * sw;
+        sum[i] = 0.0;
+    }
+    const int64_t n_tiles = (n_c + C - 1) >> lgC;
+    double2 v0[kSmallPer];
+    double v1[kSmallPer];
+    auto load = [&](int64_t tile) {
+#pragma unroll
+        for (int i = 0; i < kSmallPer; ++i) {
+            const int e = tid + kSmallThreads * i;
+            const int64_t r = (tile << lgC) + (e >> lg);
+            v0[i] = make_double2(0.0, 0.0);
+            v1[i] = 0.0;
+            if (e < total && tile < n_tiles && r < n_c) {
+                v0[i] = signal_at<PAIRS>(acc, n_t, r, 0, e & (N - 1));
+                v1[i] = signal_at<PAIRS>(acc, n_t, r, 1, e & (N - 1)).x;
+            }
+        }
+    };
+    load(blockIdx.x);
+    __syncthreads();
+    for (int64_t tile = blockIdx.x; tile < n_tiles; tile += gridDim.x) {
+        double e2 = 0.0;
+#pragma unroll
+        for (int i = 0; i < kSmallPer; ++i) {
+            const int e = tid + kSmallThreads * i;
+            if (e < total) {
+                const int at = (e & ~(N - 1)) + bitrev(e & (N - 1), lg);
+                buf[lds_at(at, lg)] = v0[i];
+                buf[lds_at(total + at, lg)] = make_double2(v1[i], 0.0);
+            }
+            if (dIdO) {  // |E|^2 of the lanes that share the cell, cell by cell
+                e2 += (v0[i].x * v0[i].x + v0[i].y * v0[i].y) + v1[i] * v1[i];
+                if (N <= kSmallThreads || ((kSmallThreads * (i + 1)) & (N - 1)) == 0) {
+                    const int width = min(N, 64);
+                    for (int m = width >> 1; m > 0; m >>= 1)
+                        e2 += __shfl_xor(e2, m);
+                    if ((tid & (width - 1)) == 0 && e < total)
+                        __hip_atomic_fetch_add(&part[e >> lg], e2, __ATOMIC_RELAXED,
+                                               __HIP_MEMORY_SCOPE_WORKGROUP);
+                    e2 = 0.0;
+                }
+            }
+        }
+        load(tile + gridDim.x);
+        lds_fft_at(buf, tw, lg, 2 * C);
+        const int64_t r0 = tile << lgC;
+#pragma unroll
+        for (int i = 0; i < kSmallPer; ++i) {
+            const int64_t r = r0 + oc[i];
+            if (oc[i] < 0 || r >= n_c)
+                continue;
+            const int b1 = oc[i] << lg, b2 = total + b1, m = om[i], mm = (N - m) & (N - 1);
+            const double2 p1 = buf[lds_at(b1 + m, lg)], q1 = buf[lds_at(b1 + mm, lg)];
+            const double2 p2 = buf[lds_at(b2 + m, lg)], q2 = buf[lds_at(b2 + mm, lg)];
+            const double p = 0.5 * ((p1.x * p1.x + p1.y * p1.y) + (q1.x * q1.x + q1.y * q1.y) +
+                                    (p2.x * p2.x + p2.y * p2.y) + (q2.x * q2.x + q2.y * q2.y));
+            const double* x = cells + 3 * r;
+            const double R2 = x[0] * x[0] + x[1] * x[1] + x[2] * x[2];
+            const double S = c * R2 / (4.0 * kPi * kPi) * W2[i] * p;
+            const int64_t cell = user_index[r];
+            if (d2I)
+                d2I[cell * n_f + m] = S;
+            sum[i] += (weights ? weights[cell] : 1.0) * S;
+        }
+        if (dIdO && tid < C) {
+            if (r0 + tid < n_c) {
+                const double* x = cells + 3 * (r0 + tid);
+                const double R2 = x[0] * x[0] + x[1] * x[1] + x[2] * x[2];
+                dIdO[user_index[r0 + tid]] = c * R2 / (4.0 * kPi) * part[tid] * dt;
+            }
+            part[tid] = 0.0;
+        }
+        __syncthreads();  // buf and part are filled again
+    }
+    if (!sums)
+        return;
+    // the workgroup's part of dI/domega: its cells' sums added up in LDS
+    double* s = reinterpret_cast<double*>(buf);
+    for (int m = tid; m < n_f; m += kSmallThreads)
+        s[m] = 0.0;
+    __syncthreads();
+#pragma unroll
+    for (int i = 0; i < kSmallPer; ++i)
+        if (oc[i] >= 0)
+            __hip_atomic_fetch_add(s + om[i], sum[i], __ATOMIC_RELAXED,
+                                   __HIP_MEMORY_SCOPE_WORKGROUP);
+    __syncthreads();
+    for (int m = tid; m < n_f; m += kSmallThreads)
+        sums[(int64_t)blockIdx.x * n_f + m] = s[m];
+}
+
+// dI/domega from the workgroups' parts [n][n_f] (adding all of them to it atomically,
+// hundreds to an address, took longer than the transforms of a small detector):
+// 32 frequencies a workgroup, 32 threads to each
+__global__ __launch_bounds__(1024) void spec_sums_kernel(const double* __restrict__ sums, int n,
+                                                         int n_f, double* __restrict__ dIdw)
+{
+    __shared__ double red[32][33];
+    const int m = blockIdx.x * 32 + threadIdx.x % 32;
+    const int k = threadIdx.x / 32;
+    double v = 0.0;
+    if (m < n_f)
+        for (int i = k; i < n; i += 32)
+            v += sums[(int64_t)i * n_f + m];
+    red[k][threadIdx.x % 32] = v;
+    __syncthreads();
+    if (k == 0 && m < n_f) {
+        for (int i = 1; i < 32; ++i)
+            v += red[i][threadIdx.x];
+        dIdw[m] = v;
     }
 }
 
@@ -569,7 +751,7 @@ __global__ __launch_bounds__(256) void spec_power_kernel(
         unsafeAtomicAdd(dIdw + m, sum);
 }
 
-// Power spectra from Qt (row-major Q of spec_rows_q_kernel, N1 = 2^lg1 rows of
+// Power spectra from Qt (row-major Q of spec_rows_q32_kernel, N1 = 2^lg1 rows of
 // N2 = 2^lg2 with lg1 + lg2 = log2 N, lg2 >= 5): a workgroup takes a tile of
 // B1 = min(N1, 32) consecutive k1 by B2 = kPowerTile / B1 consecutive k2 and
 // transposes it through LDS, so that its reads (along k2, both Q(m) and
@@ -765,26 +947,42 @@ hipError_t launch_spectrum_group(const double* acc, bool pairs, int64_t n_t, int
                                  const int64_t* user_index, const double* weights, double dt,
                                  double c, double2* work0, double2* work1, double2* tables,
                                  double* d2I, double* dIdw, double* dIdO, bool* parseval_done,
-                                 bool first_group, hipStream_t s)
+                                 bool first_group, int64_t n_cus, hipStream_t s)
 {
     *parseval_done = false;
     int lg = 0;
     while (((int64_t)1 << lg) < N)
         ++lg;
+    if (N <= kFftTile) {  // all cells in one launch (the caller's group is the detector)
+        hipLaunchKernelGGL(spec_tables_kernel, dim3(20), dim3(256), 0, s, tables, lg);
+        const int lgC = std::min(kFftTileLg - lg, 6);
+        const int64_t tiles = (G + ((int64_t)1 << lgC) - 1) >> lgC;
+        const int n_f = (int)(N / 2 + 1);
+        // two workgroups a CU, what their LDS allows
+        const int64_t blocks = std::min<int64_t>(std::min<int64_t>(tiles, 2 * n_cus), kSpecParts);
+        double* sums = dIdw ? reinterpret_cast<double*>(work0) : nullptr;
+        auto kernel = pairs ? spec_small_kernel<true> : spec_small_kernel<false>;
+        hipLaunchKernelGGL(kernel, dim3((unsigned)blocks), dim3(kSmallThreads), 0, s, acc, n_t, G,
+                           lg, tables, cells, user_index, weights, dt, c, d2I, sums, dIdO);
+        if (dIdw)
+            hipLaunchKernelGGL(spec_sums_kernel, dim3((unsigned)((n_f + 31) / 32)), dim3(1024), 0,
+                               s, sums, (int)blocks, n_f, dIdw);
+        *parseval_done = true;
+        return hipGetLastError();
+    }
     if (N <= (int64_t)kFftTile * kFftTile) {
         // four-step: N1 = 2^lg1 in the columns step, N2 = 2^lg2 in the rows
         // step, both <= kFftTile; each workgroup holds kFftTile values (32 KiB
         // of LDS) plus its twiddles.  Rows of kFftTile / 2 let the rows step
         // take both signals of a cell and store Q; the columns step does the
         // same while N1 <= kFftTile / 2.
-        const int lg2 = lg <= kFftTileLg ? 0 : std::max(kFftTileLg - 1, lg - kFftTileLg);
+        const int lg2 = std::max(kFftTileLg - 1, lg - kFftTileLg);
         const int lg1 = lg - lg2;
         const int64_t n_sig = 2 * G;
         hipLaunchKernelGGL(spec_tables_kernel, dim3(20), dim3(256), 0, s, tables, lg);
         // kFftTile values and len/2 twiddles (40 KiB for len 1024: four workgroups per CU)
         const size_t lds_a = ((size_t)kFftTile + ((size_t)1 << lg1) / 2) * sizeof(double2);
-        double2* out_a = lg2 > 0 ? work0 : work1;
-        if (lg2 > 0 && lg1 < kFftTileLg) {
+        if (lg1 < kFftTileLg) {
             const int64_t tiles_per_cell = (int64_t)1 << (lg2 - (kFftTileLg - 1 - lg1));
             const int64_t tiles = G * tiles_per_cell;
             // Parseval's per-tile sums after the row step's output in work1 (G N
@@ -793,11 +991,11 @@ hipError_t launch_spectrum_group(const double* acc, bool pairs, int64_t n_t, int
             if (pairs)
                 hipLaunchKernelGGL(spec_cols2_kernel<true>, dim3((unsigned)tiles),
                                    dim3(kFftThreads), lds_a, s, acc, n_t, r0, G, lg1, lg2, tables,
-                                   out_a, part);
+                                   work0, part);
             else
                 hipLaunchKernelGGL(spec_cols2_kernel<false>, dim3((unsigned)tiles),
                                    dim3(kFftThreads), lds_a, s, acc, n_t, r0, G, lg1, lg2, tables,
-                                   out_a, part);
+                                   work0, part);
             if (part) {
                 hipLaunchKernelGGL(spec_parseval_parts_kernel, dim3((unsigned)((G + 255) / 256)),
                                    dim3(256), 0, s, part, tiles_per_cell, G, r0, cells, user_index,
@@ -810,31 +1008,23 @@ hipError_t launch_spectrum_group(const double* acc, bool pairs, int64_t n_t, int
             const unsigned blocks_a = (unsigned)((n_cols + T - 1) / T);
             if (pairs)
                 hipLaunchKernelGGL(spec_cols_kernel<true>, dim3(blocks_a), dim3(kFftThreads), lds_a,
-                                   s, acc, n_t, r0, n_sig, lg1, lg2, tables, out_a);
+                                   s, acc, n_t, r0, n_sig, lg1, lg2, tables, work0);
             else
                 hipLaunchKernelGGL(spec_cols_kernel<false>, dim3(blocks_a), dim3(kFftThreads),
-                                   lds_a, s, acc, n_t, r0, n_sig, lg1, lg2, tables, out_a);
+                                   lds_a, s, acc, n_t, r0, n_sig, lg1, lg2, tables, work0);
         }
         int lg_q1 = 0;
-        if (lg2 > 0) {
-            const size_t lds_b = ((size_t)kFftTile + ((size_t)1 << lg2) / 2) * sizeof(double2);
-            if (lg2 == 10) {
-                // rows of 1024 in registers, one wavefront per row of a cell
-                hipLaunchKernelGGL(spec_rows_q32_kernel, dim3((unsigned)(G << lg1)), dim3(64), 0,
-                                   s, work0, G, lg1, tables, reinterpret_cast<double*>(work1));
-                lg_q1 = lg1;
-            } else if (lg2 < kFftTileLg) {
-                const int64_t tiles = G * ((int64_t)1 << (lg1 - (kFftTileLg - 1 - lg2)));
-                hipLaunchKernelGGL(spec_rows_q_kernel, dim3((unsigned)tiles), dim3(kFftThreads),
-                                   lds_b, s, work0, G, lg1, lg2, tables,
-                                   reinterpret_cast<double*>(work1));
-                lg_q1 = lg1;
-            } else {
-                const int R = kFftTile >> lg2;
-                const unsigned blocks_b = (unsigned)(n_sig * (((int64_t)1 << lg1) / R));
-                hipLaunchKernelGGL(spec_rows_kernel, dim3(blocks_b), dim3(kFftThreads), lds_b, s,
-                                   work0, n_sig, lg1, lg2, tables, work1);
-            }
+        const size_t lds_b = ((size_t)kFftTile + ((size_t)1 << lg2) / 2) * sizeof(double2);
+        if (lg2 == 10) {
+            // rows of 1024 in registers, one wavefront per row of a cell
+            hipLaunchKernelGGL(spec_rows_q32_kernel, dim3((unsigned)(G << lg1)), dim3(64), 0,
+                               s, work0, G, lg1, tables, reinterpret_cast<double*>(work1));
+            lg_q1 = lg1;
+        } else {
+            const int R = kFftTile >> lg2;
+            const unsigned blocks_b = (unsigned)(n_sig * (((int64_t)1 << lg1) / R));
+            hipLaunchKernelGGL(spec_rows_kernel, dim3(blocks_b), dim3(kFftThreads), lds_b, s,
+                               work0, n_sig, lg1, lg2, tables, work1);
         }
         return launch_power(work1, lg_q1, N, G, r0, cells, user_index, weights, dt, c, d2I, dIdw,
                             first_group, s);
