@@ -186,7 +186,8 @@ inline int64_t min_group_particles(const DepositJob& job)
     return 2 * (int64_t)job.groups;
 }
 
-hipError_t launch_zero(double* p, int64_t n, hipStream_t s);
+// clears a detector's n accumulator words and its kCounters counters
+hipError_t launch_reset(double* p, int64_t n, unsigned long long* counters, hipStream_t s);
 hipError_t launch_zero_u64(unsigned long long* p, int64_t n, hipStream_t s);
 hipError_t launch_kinematics(const DepositJob& job, int mode, hipStream_t s);
 hipError_t launch_order(const DepositJob& job, hipStream_t s);
@@ -239,7 +240,7 @@ hipError_t launch_spectrum_group(const double* acc, bool pairs, int64_t n_t, int
 // Transforms up to this length take all cells at once (r0 = 0, G = n_c), with at
 // most kSpecParts workgroups, whose parts of dI/domega (N/2 + 1 doubles each) are in
 // work0.
-constexpr int64_t kSpecOneLaunch = 2048;
+constexpr int64_t kSpecOneLaunch = 4096;
 constexpr int64_t kSpecParts = 1024;
 hipError_t launch_spectrum_parseval(const double* acc, bool pairs, int64_t n_c, int64_t n_t,
                                     const double* cells, const int64_t* user_index, double dt,

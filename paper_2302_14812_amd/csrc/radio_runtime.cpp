@@ -703,6 +703,23 @@ int enqueue_batch(radio_detector* const* dets, const radio_chunk* chunks, int n,
         double cost;
         int mode;
     };
+    // runs per item: items of similar work, and short (see kMinItemBatches)
+    int64_t n_items = 0;
+    for (radio::DepositJob& J : A->h_jobs) {
+        const double run_work = (double)J.tile_cells * (double)J.n_p * (double)J.run_l;
+        const int64_t n_batches = (J.n_p + J.groups - 1) / J.groups;
+        const int64_t rps_short = (radio::kMinItemBatches + n_batches - 1) / n_batches;
+        int64_t rps = std::min<int64_t>((int64_t)std::ceil(item_work / run_work), rps_short);
+        rps = std::max<int64_t>(1, std::min<int64_t>(rps, J.n_runs));
+        J.runs_per_split = rps;
+        J.n_splits = (J.n_runs + rps - 1) / rps;
+        n_items += J.n_splits * J.n_tiles;
+    }
+    // fewer than two rounds of resident workgroups (a run-time block of one run, few
+    // tiles): ranges of a tile's particles as well, of at least 16 batches, as
+    // plan_job cuts a single deposit (electrons in a plane
+    // wave, 8699 x 16 steps x 97 x 67 cells, double: 15.7 -> 5.8 ms)
+    const int64_t parts = std::max<int64_t>(1, (int64_t)std::ceil(2.0 * resident / (double)n_items));
     std::vector<Item> items;
     size_t ro = 0, po = 0, so = 0;
     for (size_t j = 0; j < A->h_jobs.size(); ++j) {
@@ -715,20 +732,15 @@ int enqueue_batch(radio_detector* const* dets, const radio_chunk* chunks, int n,
         po += (size_t)(J.n_groups * J.n_tiles * J.n_p);
         so += (size_t)J.n_tiles;
         const double run_work = (double)J.tile_cells * (double)J.n_p * (double)J.run_l;
-        // items of similar work, and short (see kMinItemBatches)
         const int64_t n_batches = (J.n_p + J.groups - 1) / J.groups;
-        const int64_t rps_short = (radio::kMinItemBatches + n_batches - 1) / n_batches;
-        int64_t rps = std::min<int64_t>((int64_t)std::ceil(item_work / run_work), rps_short);
-        rps = std::max<int64_t>(1, std::min<int64_t>(rps, J.n_runs));
-        J.runs_per_split = rps;
-        J.n_splits = (J.n_runs + rps - 1) / rps;
-        radio::set_parts(J, 1);  // batch items cover all of a tile's particles
+        radio::set_parts(J, std::min<int64_t>(parts, n_batches / 16));
         const int mode = radio::kernel_variant(prec, J);  // kernel variant
         for (int64_t sp = 0; sp < J.n_splits; ++sp) {
-            const int64_t runs = std::min<int64_t>(rps, J.n_runs - sp * rps);
+            const int64_t runs = std::min<int64_t>(J.runs_per_split, J.n_runs - sp * J.runs_per_split);
             for (int64_t t = 0; t < J.n_tiles; ++t)
-                items.push_back({{(int32_t)j, (int32_t)t, (int32_t)sp, 0},
-                                 (double)runs * run_work, mode});
+                for (int64_t pt = 0; pt < J.n_parts; ++pt)
+                    items.push_back({{(int32_t)j, (int32_t)t, (int32_t)sp, (int32_t)pt},
+                                     (double)runs * run_work / (double)J.n_parts, mode});
         }
         if (radio::launch_kinematics(J, prec, s) != hipSuccess ||
             radio::launch_order(J, s) != hipSuccess ||
@@ -902,8 +914,7 @@ int radio_detector_create(const radio_detector_desc* desc, void* stream, radio_d
                        hipMemcpyHostToDevice, s) != hipSuccess ||
         hipMemcpyAsync(det->d_user_index, user.data(), (size_t)n_c * sizeof(int64_t),
                        hipMemcpyHostToDevice, s) != hipSuccess ||
-        radio::launch_zero(det->d_acc, n_c * det->n_t * 6, s) != hipSuccess ||
-        radio::launch_zero_u64(det->d_counters, radio::kCounters, s) != hipSuccess ||
+        radio::launch_reset(det->d_acc, n_c * det->n_t * 6, det->d_counters, s) != hipSuccess ||
         hipStreamSynchronize(s) != hipSuccess) {  // the host vectors are pageable: finish
         radio_detector_destroy(det);
         return RADIO_EDEVICE;
@@ -952,8 +963,7 @@ int radio_detector_reset(radio_detector* det, void* stream)
     if (!g.ok())
         return RADIO_EDEVICE;
     hipStream_t s = (hipStream_t)stream;
-    if (radio::launch_zero(det->d_acc, det->n_c * det->n_t * 6, s) != hipSuccess ||
-        radio::launch_zero_u64(det->d_counters, radio::kCounters, s) != hipSuccess)
+    if (radio::launch_reset(det->d_acc, det->n_c * det->n_t * 6, det->d_counters, s) != hipSuccess)
         return RADIO_EDEVICE;
     det->interactions = 0;
     det->chunks = 0;

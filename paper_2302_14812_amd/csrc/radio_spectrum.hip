@@ -28,7 +28,7 @@
 //                      transforms the rows of both signals of a cell together
 //                      and stores only Q, row-major (8 bytes a frequency
 //                      instead of 32);
-//   spec_small_kernel  for N <= kFftTile: all of it in one pass, cell by cell;
+//   spec_small_kernel  for N <= 2 kFftTile: all of it in one pass, cell by cell;
 //   spec_load_kernel + spec_fft_pass   for N > kFftTile^2: packing, then
 //                      log2(N) radix-2 Stockham passes between two buffers;
 //   spec_power_kernel  a thread per frequency and block of cells: the power
@@ -89,7 +89,7 @@ __device__ __forceinline__ double2 cmul(double2 a, double2 b)
 constexpr int kTabLo = kFftTile / 2;
 constexpr int kTabHi = kTabLo + kFftTile;
 static_assert(kTabHi + kFftTile <= kSpecTableValues, "twiddle table layout");
-static_assert(kSpecOneLaunch == kFftTile, "one launch for what fits a tile");
+static_assert(kSpecOneLaunch == 2 * kFftTile, "spec_small_kernel's lengths");
 
 __global__ __launch_bounds__(256) void spec_tables_kernel(double2* __restrict__ tab, int lg)
 {
@@ -428,7 +428,7 @@ __global__ __launch_bounds__(64) void spec_rows_q32_kernel(const double2* __rest
 }
 
 // ---------------------------------------------------------------------------
-// transforms of up to kFftTile slots
+// transforms of up to 2 kFftTile slots
 // ---------------------------------------------------------------------------
 
 // The whole spectrum of C = min(kFftTile / N, 64) cells at a time in one kernel:
@@ -441,9 +441,11 @@ __global__ __launch_bounds__(64) void spec_rows_q32_kernel(const double2* __rest
 // (2.9 TB/s).  Measured against columns, power and a separate Parseval pass, which
 // wrote and read both signals' spectra between them: 16384 cells x 2048 slots with
 // weights 1.35 -> 0.56 ms a call, 4000 cells x 300 slots 94 -> 74 us, 37 x 37 41 -> 40.
-constexpr int kSmallCells = 64;                       // cells at a time, at most
-constexpr int kSmallThreads = 512;                    // four wavefronts a SIMD
-constexpr int kSmallPer = kFftTile / kSmallThreads;   // slots, and outputs, of a thread
+// LGT: log2 of the slots at a time; 2048 for transforms up to that, in 512 threads
+// (two workgroups a CU), and 4096 in 1024 threads (one): four wavefronts a SIMD.
+constexpr int kSmallCells = 64;                           // cells at a time, at most
+constexpr int kSmallPer = 4;                              // slots, and outputs, of a thread
+constexpr int small_threads(int lgt) { return (1 << lgt) / kSmallPer; }
 
 // Position of value i of a transform of 2^lg in LDS.  Sixteen values span the
 // banks, and sixteen consecutive threads reach a pass's values at strides of 4 or 16
@@ -458,13 +460,14 @@ __device__ __forceinline__ int lds_at(int i, int lg)
 
 // lds_fft on values kept at lds_at(); tw holds the first quarter of the circle, all
 // that two stages per pass read.
+template <int THREADS>
 __device__ __forceinline__ void lds_fft_at(double2* buf, const double2* tw, int lg, int T)
 {
     const int len = 1 << lg;
     int lgh = 0;
     if (lg & 1) {
         __syncthreads();
-        for (int b = threadIdx.x; b < T * (len >> 1); b += kSmallThreads) {
+        for (int b = threadIdx.x; b < T * (len >> 1); b += THREADS) {
             double2* x = buf + lds_at(2 * b, lg);
             double2* y = buf + lds_at(2 * b + 1, lg);
             const double2 a = *x, c = *y;
@@ -478,7 +481,7 @@ __device__ __forceinline__ void lds_fft_at(double2* buf, const double2* tw, int 
         const int h = 1 << lgh;
         const int step = len >> (lgh + 2);  // W_4h^k = tw[k step]
 #pragma unroll 1
-        for (int b = threadIdx.x; b < T * (len >> 2); b += kSmallThreads) {
+        for (int b = threadIdx.x; b < T * (len >> 2); b += THREADS) {
             const int k = b & (h - 1);
             const int i = ((b >> lgh) << (lgh + 2)) + k;
             double2* x0 = buf + lds_at(i, lg);
@@ -504,24 +507,26 @@ __device__ __forceinline__ void lds_fft_at(double2* buf, const double2* tw, int 
     __syncthreads();
 }
 
-template <bool PAIRS>
-__global__ __launch_bounds__(kSmallThreads, 4) void spec_small_kernel(
+template <bool PAIRS, int LGT>
+__global__ __launch_bounds__(small_threads(LGT), 4) void spec_small_kernel(
     const double* __restrict__ acc, int64_t n_t, int64_t n_c, int lg,
     const double2* __restrict__ tab, const double* __restrict__ cells,
     const int64_t* __restrict__ user_index, const double* __restrict__ weights, double dt, double c,
     double* __restrict__ d2I, double* __restrict__ sums, double* __restrict__ dIdO)
 {
-    __shared__ double2 buf[2 * kFftTile];  // [signal][cell][slot], at lds_at()
-    __shared__ double2 tw[kFftTile / 4];
+    constexpr int kSmallThreads = small_threads(LGT);
+    constexpr int kTile = 1 << LGT;
+    __shared__ double2 buf[2 * kTile];  // [signal][cell][slot], at lds_at()
+    __shared__ double2 tw[kTile / 4];
     __shared__ double part[kSmallCells];   // sums of |E|^2
     const int tid = threadIdx.x;
     const int N = 1 << lg;
-    const int lgC = min(kFftTileLg - lg, 6);
+    const int lgC = min(LGT - lg, 6);
     const int C = 1 << lgC;
-    const int total = C << lg;             // slots at a time (at most kFftTile)
+    const int total = C << lg;             // slots at a time (at most kTile)
     const int n_f = N / 2 + 1;
     for (int k = tid; k < N / 4; k += kSmallThreads)
-        tw[k] = tab[k << (kFftTileLg - lg)];
+        tw[k] = lg <= kFftTileLg ? tab[k << (kFftTileLg - lg)] : twiddle(tab, k, (lg + 1) / 2);
     if (tid < kSmallCells)
         part[tid] = 0.0;
     // the thread's outputs: cell of the tile, frequency, |(e^{-i w dt} - 1)/(-i w)|^2
@@ -579,7 +584,7 @@ __global__ __launch_bounds__(kSmallThreads, 4) void spec_small_kernel(
             }
         }
         load(tile + gridDim.x);
-        lds_fft_at(buf, tw, lg, 2 * C);
+        lds_fft_at<kSmallThreads>(buf, tw, lg, 2 * C);
         const int64_t r0 = tile << lgC;
 #pragma unroll
         for (int i = 0; i < kSmallPer; ++i) {
@@ -953,17 +958,23 @@ hipError_t launch_spectrum_group(const double* acc, bool pairs, int64_t n_t, int
     int lg = 0;
     while (((int64_t)1 << lg) < N)
         ++lg;
-    if (N <= kFftTile) {  // all cells in one launch (the caller's group is the detector)
+    if (N <= kSpecOneLaunch) {  // all cells at once (the caller's group is the detector)
         hipLaunchKernelGGL(spec_tables_kernel, dim3(20), dim3(256), 0, s, tables, lg);
-        const int lgC = std::min(kFftTileLg - lg, 6);
+        const bool wide = N > kFftTile;
+        const int lgC = wide ? 0 : std::min(kFftTileLg - lg, 6);
         const int64_t tiles = (G + ((int64_t)1 << lgC) - 1) >> lgC;
         const int n_f = (int)(N / 2 + 1);
-        // two workgroups a CU, what their LDS allows
-        const int64_t blocks = std::min<int64_t>(std::min<int64_t>(tiles, 2 * n_cus), kSpecParts);
+        // the workgroups their LDS allows
+        const int64_t blocks =
+            std::min<int64_t>(std::min<int64_t>(tiles, (wide ? 1 : 2) * n_cus), kSpecParts);
         double* sums = dIdw ? reinterpret_cast<double*>(work0) : nullptr;
-        auto kernel = pairs ? spec_small_kernel<true> : spec_small_kernel<false>;
-        hipLaunchKernelGGL(kernel, dim3((unsigned)blocks), dim3(kSmallThreads), 0, s, acc, n_t, G,
-                           lg, tables, cells, user_index, weights, dt, c, d2I, sums, dIdO);
+        auto kernel = wide ? (pairs ? spec_small_kernel<true, kFftTileLg + 1>
+                                    : spec_small_kernel<false, kFftTileLg + 1>)
+                           : (pairs ? spec_small_kernel<true, kFftTileLg>
+                                    : spec_small_kernel<false, kFftTileLg>);
+        const unsigned threads = small_threads(wide ? kFftTileLg + 1 : kFftTileLg);
+        hipLaunchKernelGGL(kernel, dim3((unsigned)blocks), dim3(threads), 0, s, acc, n_t, G, lg,
+                           tables, cells, user_index, weights, dt, c, d2I, sums, dIdO);
         if (dIdw)
             hipLaunchKernelGGL(spec_sums_kernel, dim3((unsigned)((n_f + 31) / 32)), dim3(1024), 0,
                                s, sums, (int)blocks, n_f, dIdw);
