@@ -163,7 +163,8 @@ void set_shape(DepositJob& job, int shape);
 // target_blocks when it is positive, else into short items (a run or a few)
 // while at least `capacity` items (the workgroups resident at once) remain;
 // with fewer than two rounds of items, also into ranges of the tile's sorted
-// particles (parts of at least 16 batches).
+// particles (parts of at least four batches: of 16, a small chunk left most of the device
+// idle; 692 particles x 190 steps x 24 x 13 cells 528 -> 302 us, 720 x 16 x 41 x 26 527 -> 291).
 void plan_job(DepositJob& job, int target_blocks, int64_t capacity);
 // the tile's sorted batches in `parts` contiguous ranges (1: all of them)
 void set_parts(DepositJob& job, int64_t parts);

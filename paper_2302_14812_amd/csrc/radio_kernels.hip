@@ -2378,7 +2378,7 @@ void plan_job(DepositJob& job, int target_blocks, int64_t capacity)
     const int64_t items = job.n_tiles * job.n_splits;
     if (target_blocks <= 0 && items < 2 * capacity) {
         parts = (2 * capacity + items - 1) / items;
-        parts = std::max<int64_t>(1, std::min<int64_t>(parts, n_batches / 16));
+        parts = std::max<int64_t>(1, std::min<int64_t>(parts, n_batches / 4));
     }
     set_parts(job, parts);
 }

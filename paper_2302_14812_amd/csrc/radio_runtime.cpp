@@ -716,7 +716,7 @@ int enqueue_batch(radio_detector* const* dets, const radio_chunk* chunks, int n,
         n_items += J.n_splits * J.n_tiles;
     }
     // fewer than two rounds of resident workgroups (a run-time block of one run, few
-    // tiles): ranges of a tile's particles as well, of at least 16 batches, as
+    // tiles): ranges of a tile's particles as well, of at least four batches, as
     // plan_job cuts a single deposit (electrons in a plane
     // wave, 8699 x 16 steps x 97 x 67 cells, double: 15.7 -> 5.8 ms)
     const int64_t parts = std::max<int64_t>(1, (int64_t)std::ceil(2.0 * resident / (double)n_items));
@@ -733,7 +733,7 @@ int enqueue_batch(radio_detector* const* dets, const radio_chunk* chunks, int n,
         so += (size_t)J.n_tiles;
         const double run_work = (double)J.tile_cells * (double)J.n_p * (double)J.run_l;
         const int64_t n_batches = (J.n_p + J.groups - 1) / J.groups;
-        radio::set_parts(J, std::min<int64_t>(parts, n_batches / 16));
+        radio::set_parts(J, std::min<int64_t>(parts, n_batches / 4));
         const int mode = radio::kernel_variant(prec, J);  // kernel variant
         for (int64_t sp = 0; sp < J.n_splits; ++sp) {
             const int64_t runs = std::min<int64_t>(J.runs_per_split, J.n_runs - sp * J.runs_per_split);
