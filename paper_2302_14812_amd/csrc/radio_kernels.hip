@@ -20,7 +20,8 @@
 //
 // 3. ring_choice_kernel: per tile, whether the arrivals a batch touches fit
 //    the small LDS ring (slow advance, many segments per slot) or need the
-//    large one (a slot crossed every segment or two); it samples batches.
+//    large one (a slot crossed every segment or two), of slot values or of field
+//    jumps, with its runs staged whole or in shorter stretches; it samples batches.
 //
 // 4. deposit_kernel: one workgroup per (tile, range of runs), launched once
 //    per ring size; tiles of the other size leave at once.  Lane
@@ -35,6 +36,8 @@
 //    per-cell ring of slots in LDS that slides forward as the sorted batches
 //    advance, and only slots leaving the ring (or emissions that fall outside
 //    it) reach the detector in HBM, through atomic adds.
+//
+// A chunk of a few particles takes few_kernel alone.
 //
 // Slot accumulator.  The detector holds, per cell and slot, the sum over
 // segments of the held E and B times the segment's overlap with the slot in
@@ -238,21 +241,6 @@ __device__ __forceinline__ void global_add(RADIO_GLOBAL float* row, int j, const
 #pragma unroll
     for (int k = 0; k < 6; ++k)
         __hip_atomic_fetch_add(q + 6 + k, two_sum_err(old[k], a[k], old[k] + a[k]),
-                               __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-}
-
-// a compensated pair (hi, lo) into the HBM pair, the same way
-__device__ __forceinline__ void global_add_pair(RADIO_GLOBAL float* row, int j, const float hi[6],
-                                                const float lo[6])
-{
-    RADIO_GLOBAL float* q = row + (int64_t)j * 12;
-    float old[6];
-#pragma unroll
-    for (int k = 0; k < 6; ++k)
-        old[k] = __hip_atomic_fetch_add(q + k, hi[k], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-#pragma unroll
-    for (int k = 0; k < 6; ++k)
-        __hip_atomic_fetch_add(q + 6 + k, two_sum_err(old[k], hi[k], old[k] + hi[k]) + lo[k],
                                __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
 }
 
@@ -690,7 +678,8 @@ __device__ __forceinline__ void add_jump(RADIO_LDS double* ring, double u, const
 #pragma unroll
     for (int k = 0; k < 6; ++k) {
         const double t = d[k] * f;
-        __hip_atomic_fetch_add(q0 + k * TC, d[k] - t, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
+        __hip_atomic_fetch_add(q0 + k * TC, d[k] - t, __ATOMIC_RELAXED,
+                               __HIP_MEMORY_SCOPE_WORKGROUP);
         __hip_atomic_fetch_add(q1 + k * TC, t, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
     }
 }
