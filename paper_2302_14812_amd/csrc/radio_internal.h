@@ -90,12 +90,9 @@ constexpr int kRingSmall = RADIO_RING_SMALL;
 constexpr int kRingLarge = RADIO_RING_LARGE;
 // A tile's ring choice (DepositJob::ring_sel): the small ring, or kRingSel64 + h,
 // the large one with a run staged in 2^h stretches (arrivals so sparse that a
-// longer one spans more slots than the large ring); with kRingSelJumps the
-// large ring holds field jumps instead of slot values.
+// longer one spans more slots than the large ring).
 constexpr int kRingSel16 = 0;
 constexpr int kRingSel64 = 1;
-constexpr int kRingSelShift = 7;  // mask of kRingSel64 + h
-constexpr int kRingSelJumps = 8;
 constexpr int kMaxPartShift = 4;
 
 // One (detector, chunk) deposit as the kernels see it.  Sizes are 64-bit; the
