@@ -928,15 +928,16 @@ __global__ __launch_bounds__(256) void order_kernel(const double* __restrict__ x
                                                     int64_t steps_per_group,
                                                     const double* __restrict__ cells, int64_t n_c,
                                                     double inv_c, double inv_dt_det,
-                                                    int32_t* __restrict__ perm)
+                                                    int32_t* __restrict__ perm, int64_t item0)
 {
     __shared__ __align__(16) unsigned hist[kOrderBins];
     __shared__ double red[2][4];
     __shared__ unsigned wave_sum[4];
     const int tid = threadIdx.x;
     const int lane = tid % 64, wave = tid / 64;
-    const int64_t tile = blockIdx.x % n_tiles;
-    const int64_t group = blockIdx.x / n_tiles;
+    const int64_t item = item0 + blockIdx.x;
+    const int64_t tile = item % n_tiles;
+    const int64_t group = item / n_tiles;
     // the group's middle state
     const int64_t s_key = min(n_s, group * steps_per_group + steps_per_group / 2);
     const int64_t c0 = tile * tile_cells;
@@ -1087,7 +1088,7 @@ __global__ __launch_bounds__(256) void ring_choice_kernel(const char* __restrict
                                                           double inv_dt_det, double inv_c,
                                                           int64_t n_t, int tile_cells, int groups,
                                                           int run_l, int max_shift,
-                                                          uint8_t* __restrict__ sel)
+                                                          uint8_t* __restrict__ sel, int64_t tile0)
 {
     // one thread per sampled particle: 256 / groups sampled batches
     const int n_samples = 256 / groups;
@@ -1095,7 +1096,7 @@ __global__ __launch_bounds__(256) void ring_choice_kernel(const char* __restrict
     __shared__ int start[64][kMaxRun + 1];
     __shared__ unsigned out_count, emitted, segs, far_count[kMaxPartShift + 1];
     const int tid = threadIdx.x;
-    const int64_t tile = blockIdx.x;
+    const int64_t tile = tile0 + blockIdx.x;
     const int64_t c0 = tile * tile_cells;
     for (int i = tid; i < n_samples * (kMaxRun + 1); i += 256)
         (&start[0][0])[i] = INT_MAX;
@@ -2103,7 +2104,9 @@ __global__ void slot_coord_kernel(const double* cells, const double* pts, const 
 
 }  // namespace
 
-constexpr int64_t kMaxDepositGrid = int64_t(1) << 22;  // workgroups of one deposit launch
+// workgroups of one launch: what has more of them runs in several (a launch takes fewer
+// than 2^32 threads)
+constexpr int64_t kMaxDepositGrid = int64_t(1) << 22;
 
 void set_shape(DepositJob& job, int shape)
 {
@@ -2216,27 +2219,31 @@ hipError_t launch_kinematics(const DepositJob& job, int mode, hipStream_t s)
 hipError_t launch_order(const DepositJob& job, hipStream_t s)
 {
     auto kernel = job.n_p <= 256 * kOrderHeld ? order_kernel<true> : order_kernel<false>;
-    hipLaunchKernelGGL(kernel, dim3((unsigned)(job.n_tiles * job.n_groups)), dim3(256), 0, s,
-                       job.x, job.n_p, job.n_s, job.xs_stride, job.n_tiles,
-                       (int64_t)job.tile_cells, job.runs_per_group * job.run_l,
-                       job.cells, job.n_c, job.inv_c, job.inv_dt_det, job.perm);
+    // a long chunk has an order per tile for every run or two of it
+    const int64_t n_items = job.n_tiles * job.n_groups;
+    for (int64_t item0 = 0; item0 < n_items; item0 += kMaxDepositGrid)
+        hipLaunchKernelGGL(kernel,
+                           dim3((unsigned)std::min<int64_t>(n_items - item0, kMaxDepositGrid)),
+                           dim3(256), 0, s, job.x, job.n_p, job.n_s, job.xs_stride, job.n_tiles,
+                           (int64_t)job.tile_cells, job.runs_per_group * job.run_l, job.cells,
+                           job.n_c, job.inv_c, job.inv_dt_det, job.perm, item0);
     return hipGetLastError();
 }
 
 hipError_t launch_ring_choice(const DepositJob& job, int mode, hipStream_t s)
 {
-    if (job.n_tiles <= 0)
-        return hipSuccess;
     int max_shift = 0;  // stretches down to one segment
     while (max_shift < kMaxPartShift && (job.run_l >> (max_shift + 1)) > 0)
         ++max_shift;
-    hipLaunchKernelGGL(ring_choice_kernel, dim3((unsigned)job.n_tiles), dim3(256), 0, s,
-                       reinterpret_cast<const char*>(job.recs), (int64_t)rec_bytes(mode),
-                       job.perm, job.n_tiles, job.runs_per_group, job.cells, job.far, job.n_c,
-                       job.n_p, job.n_s, job.n_runs,
-                       job.t_first,
-                       job.s0, job.dt, job.t0, job.inv_dt_det, job.inv_c, job.n_t,
-                       (int)job.tile_cells, (int)job.groups, (int)job.run_l, max_shift, job.ring_sel);
+    for (int64_t tile0 = 0; tile0 < job.n_tiles; tile0 += kMaxDepositGrid)
+        hipLaunchKernelGGL(ring_choice_kernel,
+                           dim3((unsigned)std::min<int64_t>(job.n_tiles - tile0, kMaxDepositGrid)),
+                           dim3(256), 0, s, reinterpret_cast<const char*>(job.recs),
+                           (int64_t)rec_bytes(mode), job.perm, job.n_tiles, job.runs_per_group,
+                           job.cells, job.far, job.n_c, job.n_p, job.n_s, job.n_runs, job.t_first,
+                           job.s0, job.dt, job.t0, job.inv_dt_det, job.inv_c, job.n_t,
+                           (int)job.tile_cells, (int)job.groups, (int)job.run_l, max_shift,
+                           job.ring_sel, tile0);
     return hipGetLastError();
 }
 

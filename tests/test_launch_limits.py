@@ -1,0 +1,118 @@
+"""Launches of the per-tile kernels on the CPU: a launch takes fewer than 2^32 threads.
+
+The library's host code (launch_order, launch_ring_choice and the planner in
+radio_kernels.hip, host pass only) is linked with a driver that has its own
+hipLaunchKernel, which notes the grid and the first work item of each launch
+instead of launching.  Chunks whose particle orders or tiles need more threads than
+one launch takes have to arrive in several that together cover every one once.
+"""
+import os
+import shutil
+import subprocess
+
+import pytest
+
+ROOT = os.path.dirname(os.path.dirname(os.path.abspath(__file__)))
+CSRC = os.path.join(ROOT, "paper_2302_14812_amd", "csrc")
+HIPCC = os.environ.get("HIPCC", "/opt/rocm/bin/hipcc")
+
+DRIVER = r"""
+#include <hip/hip_runtime.h>
+#include <cstdio>
+#include "radio_internal.h"
+static long long g_threads, g_most, g_next, g_bad, g_launches;
+static int g_item_arg;
+static dim3 g_grid, g_block;
+extern "C" {
+void** __hipRegisterFatBinary(const void*) { static void* p; return &p; }
+void __hipUnregisterFatBinary(void**) {}
+void __hipRegisterFunction(void**, const void*, char*, const char*, unsigned, void*, void*, void*,
+                           void*, int*) {}
+void __hipRegisterVar(void**, void*, char*, char*, int, size_t, int, int) {}
+hipError_t __hipPushCallConfiguration(dim3 grid, dim3 block, size_t, hipStream_t)
+{
+    g_grid = grid; g_block = block;
+    return hipSuccess;
+}
+hipError_t __hipPopCallConfiguration(dim3* grid, dim3* block, size_t* shmem, hipStream_t* s)
+{
+    *grid = g_grid; *block = g_block; *shmem = 0; *s = nullptr;
+    return hipSuccess;
+}
+hipError_t hipLaunchKernel(const void*, dim3 grid, dim3 block, void** args, size_t, hipStream_t)
+{
+    const long long threads = (long long)grid.x * block.x;
+    g_threads += threads;
+    g_most = threads > g_most ? threads : g_most;
+    if (*(long long*)args[g_item_arg] != g_next)
+        ++g_bad;  // not where the last launch ended
+    g_next += grid.x;
+    ++g_launches;
+    return hipSuccess;
+}
+hipError_t hipGetLastError() { return hipSuccess; }
+hipError_t hipOccupancyMaxActiveBlocksPerMultiprocessor(int* n, const void*, int, size_t)
+{
+    *n = 4;
+    return hipSuccess;
+}
+}
+static void show(const char* what, long long items, int arg)
+{
+    printf("%s items=%lld covered=%lld bad=%lld most=%lld launches=%lld\n", what, items, g_next,
+           g_bad, g_most, g_launches);
+    g_threads = g_most = g_next = g_bad = g_launches = 0;
+}
+int main()
+{
+    using namespace radio;
+    const long long cases[][3] = {  // particles, steps, cells
+        {256, 1200000, 4096}, {300, 4000000, 16384}, {32, 1100000, 4096}, {40, 2000000, 4096},
+        {255, 1300000, 8192}, {1, 1, 1}, {1000, 2048, 16384}, {7, 100, 300000000}};
+    for (auto& c : cases)
+        for (int mode = 0; mode < 2; ++mode)
+            for (int shape = 0; shape < kShapes; ++shape) {
+                DepositJob J{};
+                J.n_p = c[0]; J.n_s = c[1]; J.n_c = c[2]; J.n_t = 64;
+                set_shape(J, shape);
+                plan_job(J, 0, 1024);
+                set_groups(J, max_order_groups(J, rec_bytes(mode), 0));
+                g_item_arg = ORDER_ITEM;
+                if (launch_order(J, nullptr) != hipSuccess) return 1;
+                show("order", J.n_tiles * J.n_groups, 0);
+                g_item_arg = CHOICE_ITEM;
+                if (launch_ring_choice(J, mode, nullptr) != hipSuccess) return 1;
+                show("choice", J.n_tiles, 0);
+            }
+    return 0;
+}
+"""
+
+# place of the first work item among each kernel's arguments (their last)
+ORDER_ITEM, CHOICE_ITEM = 12, 23
+
+
+@pytest.mark.skipif(not os.path.exists(HIPCC) or shutil.which(HIPCC) is None, reason="needs hipcc")
+def test_launches_stay_under_the_thread_limit(tmp_path):
+    drv = tmp_path / "driver.cpp"
+    drv.write_text(DRIVER)
+    common = [HIPCC, "-O1", "-std=c++17", "--offload-arch=gfx950", "--cuda-host-only", "-x", "hip",
+              f"-DORDER_ITEM={ORDER_ITEM}", f"-DCHOICE_ITEM={CHOICE_ITEM}",
+              "-I", os.path.join(ROOT, "include"), "-I", CSRC, "-c"]
+    objs = []
+    for src in (str(drv), os.path.join(CSRC, "radio_kernels.hip")):
+        obj = str(tmp_path / (os.path.basename(src) + ".o"))
+        subprocess.run(common + [src, "-o", obj], check=True, capture_output=True)
+        objs.append(obj)
+    exe = str(tmp_path / "driver")
+    # nothing is launched, so the kernels' code is not linked in
+    subprocess.run(["g++"] + objs + ["-Wl,--unresolved-symbols=ignore-all", "-no-pie", "-o", exe],
+                   check=True, capture_output=True)
+    out = subprocess.run([exe], check=True, capture_output=True, text=True, timeout=60).stdout
+    print(out)
+    lines = [dict(f.split("=") for f in ln.split()[1:]) for ln in out.splitlines()]
+    assert len(lines) >= 2 * 8 * 2
+    assert any(int(d["items"]) * 256 >= 2**32 for d in lines)  # the limit is met
+    for d in lines:
+        assert int(d["most"]) < 2**32, d
+        assert int(d["covered"]) == int(d["items"]) and d["bad"] == "0", d
