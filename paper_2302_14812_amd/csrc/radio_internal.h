@@ -170,18 +170,21 @@ void set_parts(DepositJob& job, int64_t parts);
 // re-sorted along it.  max_order_groups is how many orders fit the budget
 // (budget_mib, or when 0 the size of the chunk's state records and at least
 // 1 GiB); set_groups spreads the job's runs over at most that many groups.
-// Chunks of fewer than two batches of particles keep one order.
+// Chunks of fewer than 16 batches of particles keep one order.
 int64_t max_order_groups(const DepositJob& job, size_t rec_bytes, int64_t budget_mib);
 void set_groups(DepositJob& job, int64_t max_groups);
 // Runs per order group that a deposit keeps to, by depositing a longer chunk
 // in time slices whose orders fit the budget; particles below which a chunk
-// keeps a single order (two batches of the job's shape: with fewer there is nothing to
-// sort; uneven sets of 54-434 particles gained 1.3% from orders below 16 batches, whose
-// arrival offsets drift apart over a long chunk too).
+// keeps a single order (16 batches of the job's shape).  Sorting these chunks again too,
+// from two batches on, cost 1 to 4% where arrivals are dense (54 particles x 2000
+// steps x 64 x 64 cells x 200 slots, mixed: 2.39 against 2.29 ms), won 6 to 15% only
+// where a step crosses several slots (200 particles, 4000 slots: 55.4 against 63.6),
+// and its orders took 0.8 GB for a chunk whose one order is 0.1 MB (32 particles x
+// 2e5 steps x 16384 cells).
 constexpr int64_t kRunsPerGroup = 2;
 inline int64_t min_group_particles(const DepositJob& job)
 {
-    return 2 * (int64_t)job.groups;
+    return 16 * (int64_t)job.groups;
 }
 
 // clears a detector's n accumulator words and its kCounters counters

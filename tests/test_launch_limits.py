@@ -7,7 +7,6 @@ instead of launching.  Chunks whose particle orders or tiles need more threads t
 one launch takes have to arrive in several that together cover every one once.
 """
 import os
-import shutil
 import subprocess
 
 import pytest
@@ -83,6 +82,9 @@ int main()
                 g_item_arg = CHOICE_ITEM;
                 if (launch_ring_choice(J, mode, nullptr) != hipSuccess) return 1;
                 show("choice", J.n_tiles, 0);
+                printf("plan batches=%lld groups=%lld runs=%lld\n",
+                       (long long)((J.n_p + J.groups - 1) / J.groups), (long long)J.n_groups,
+                       (long long)J.n_runs);
             }
     return 0;
 }
@@ -92,27 +94,44 @@ int main()
 ORDER_ITEM, CHOICE_ITEM = 12, 23
 
 
-@pytest.mark.skipif(not os.path.exists(HIPCC) or shutil.which(HIPCC) is None, reason="needs hipcc")
-def test_launches_stay_under_the_thread_limit(tmp_path):
-    drv = tmp_path / "driver.cpp"
+@pytest.fixture(scope="module")
+def lines(tmp_path_factory):
+    if not os.path.exists(HIPCC):
+        pytest.skip("needs hipcc")
+    tmp = tmp_path_factory.mktemp("limits")
+    drv = tmp / "driver.cpp"
     drv.write_text(DRIVER)
     common = [HIPCC, "-O1", "-std=c++17", "--offload-arch=gfx950", "--cuda-host-only", "-x", "hip",
               f"-DORDER_ITEM={ORDER_ITEM}", f"-DCHOICE_ITEM={CHOICE_ITEM}",
               "-I", os.path.join(ROOT, "include"), "-I", CSRC, "-c"]
     objs = []
     for src in (str(drv), os.path.join(CSRC, "radio_kernels.hip")):
-        obj = str(tmp_path / (os.path.basename(src) + ".o"))
+        obj = str(tmp / (os.path.basename(src) + ".o"))
         subprocess.run(common + [src, "-o", obj], check=True, capture_output=True)
         objs.append(obj)
-    exe = str(tmp_path / "driver")
+    exe = str(tmp / "driver")
     # nothing is launched, so the kernels' code is not linked in
     subprocess.run(["g++"] + objs + ["-Wl,--unresolved-symbols=ignore-all", "-no-pie", "-o", exe],
                    check=True, capture_output=True)
     out = subprocess.run([exe], check=True, capture_output=True, text=True, timeout=60).stdout
-    print(out)
-    lines = [dict(f.split("=") for f in ln.split()[1:]) for ln in out.splitlines()]
-    assert len(lines) >= 2 * 8 * 2
-    assert any(int(d["items"]) * 256 >= 2**32 for d in lines)  # the limit is met
-    for d in lines:
-        assert int(d["most"]) < 2**32, d
-        assert int(d["covered"]) == int(d["items"]) and d["bad"] == "0", d
+    return [(ln.split()[0], {k: int(v) for k, v in (f.split("=") for f in ln.split()[1:])})
+            for ln in out.splitlines()]
+
+
+def test_launches_stay_under_the_thread_limit(lines):
+    launches = [d for what, d in lines if what != "plan"]
+    assert len(launches) >= 2 * 8 * 2
+    assert any(d["items"] * 256 >= 2**32 for d in launches)  # the limit is met
+    for d in launches:
+        assert d["most"] < 2**32, d
+        assert d["covered"] == d["items"] and d["bad"] == 0, d
+
+
+def test_few_batches_keep_one_order(lines):
+    """A chunk of fewer than 16 batches of particles keeps one order a tile, a
+    workspace that does not grow with its steps; a longer one is sorted again."""
+    plans = [d for what, d in lines if what == "plan"]
+    few = [d for d in plans if d["batches"] < 16]
+    assert max(d["runs"] for d in few) > 60000
+    assert all(d["groups"] == 1 for d in few), few
+    assert any(d["groups"] > 1 for d in plans)
