@@ -195,11 +195,23 @@ hipError_t launch_order(const DepositJob& job, hipStream_t s);
 hipError_t launch_ring_choice(const DepositJob& job, int mode, hipStream_t s);
 hipError_t launch_deposit(const DepositJob& job, int mode, int64_t max_grid, hipStream_t s);
 // The deposit of a few particles (few_kernel): one launch without a workspace, for
-// jobs of at most kFewParticles particles with the default geometry and hold.  The
-// line: circular orbits, 2000 steps x 32 x 32 cells, double, 6 particles 169 us
-// against 184 by the general kernels, 8 particles 223 against 188; an undulator's
-// 2048 steps x 64 x 64 cells x 64 slots 526 against 533 and 674 against 539.
+// jobs of at most kFewParticles particles with the default geometry and hold.  Its
+// time grows with the particles (1e11 interactions/s, less where slots are many),
+// that of the general kernels, whose batch takes 16, hardly does, but it grows with
+// the slots a step crosses and has four launches.  So from kFewAlways on, much work
+// at dense arrivals, which merge in the rings (slots of kFewDense steps or more, or
+// kFewCrowded steps and more to a slot of the window), takes the general kernels.  Circular orbits, double, few against general: 800 steps x 128
+// x 128 cells x 64 slots 405 against 503 us with 3 particles, 535 against 508 with 4,
+// 792 against 664 with 6 (mixed 383 against 537, 507 against 542, 753 against 606);
+// 800 x 32 x 32 cells with 6 79 against 95; an undulator's 2000 steps x 64 x 64 cells
+// x 1000 slots with 6 595 against 2070, 500 x 128 x 128 cells x 32 slots with 6 475
+// against 406; one step x 512 x 512 cells with 6 850 against
+// 920.
 constexpr int64_t kFewParticles = 6;
+constexpr int64_t kFewAlways = 3;
+constexpr double kFewDense = 2.0;  // slot width in steps
+constexpr int64_t kFewCrowded = 8;  // steps per slot of the window
+constexpr double kFewWork = 1.0e7;  // interactions
 constexpr int64_t kFewCells = 8;  // cells a wavefront takes at most
 bool few_particles(const DepositJob& job);
 hipError_t launch_few(const DepositJob& job, int mode, int64_t n_cus, hipStream_t s);

@@ -2337,7 +2337,12 @@ hipError_t launch_deposit(const DepositJob& job, int mode, int64_t max_grid, hip
 
 bool few_particles(const DepositJob& job)
 {
-    return job.n_p <= kFewParticles && job.hold == 0 && !job.potentials && !job.far;
+    if (job.n_p > kFewParticles || job.hold != 0 || job.potentials || job.far)
+        return false;
+    // dense: slots of several steps, or more segments than the window's slots can take
+    const bool dense = job.dt_det >= kFewDense * job.dt || job.n_s >= kFewCrowded * job.n_t;
+    return job.n_p <= kFewAlways || !dense ||
+           (double)job.n_p * (double)job.n_s * (double)job.n_c <= kFewWork;
 }
 
 hipError_t launch_few(const DepositJob& job, int mode, int64_t n_cus, hipStream_t s)

@@ -6,39 +6,14 @@ hipLaunchKernel, which notes the grid and the first work item of each launch
 instead of launching.  Chunks whose particle orders or tiles need more threads than
 one launch takes have to arrive in several that together cover every one once.
 """
-import os
-import subprocess
-
 import pytest
 
-ROOT = os.path.dirname(os.path.dirname(os.path.abspath(__file__)))
-CSRC = os.path.join(ROOT, "paper_2302_14812_amd", "csrc")
-HIPCC = os.environ.get("HIPCC", "/opt/rocm/bin/hipcc")
+import host_driver
 
 DRIVER = r"""
-#include <hip/hip_runtime.h>
-#include <cstdio>
-#include "radio_internal.h"
 static long long g_threads, g_most, g_next, g_bad, g_launches;
 static int g_item_arg;
-static dim3 g_grid, g_block;
-extern "C" {
-void** __hipRegisterFatBinary(const void*) { static void* p; return &p; }
-void __hipUnregisterFatBinary(void**) {}
-void __hipRegisterFunction(void**, const void*, char*, const char*, unsigned, void*, void*, void*,
-                           void*, int*) {}
-void __hipRegisterVar(void**, void*, char*, char*, int, size_t, int, int) {}
-hipError_t __hipPushCallConfiguration(dim3 grid, dim3 block, size_t, hipStream_t)
-{
-    g_grid = grid; g_block = block;
-    return hipSuccess;
-}
-hipError_t __hipPopCallConfiguration(dim3* grid, dim3* block, size_t* shmem, hipStream_t* s)
-{
-    *grid = g_grid; *block = g_block; *shmem = 0; *s = nullptr;
-    return hipSuccess;
-}
-hipError_t hipLaunchKernel(const void*, dim3 grid, dim3 block, void** args, size_t, hipStream_t)
+extern "C" hipError_t hipLaunchKernel(const void*, dim3 grid, dim3 block, void** args, size_t, hipStream_t)
 {
     const long long threads = (long long)grid.x * block.x;
     g_threads += threads;
@@ -48,13 +23,6 @@ hipError_t hipLaunchKernel(const void*, dim3 grid, dim3 block, void** args, size
     g_next += grid.x;
     ++g_launches;
     return hipSuccess;
-}
-hipError_t hipGetLastError() { return hipSuccess; }
-hipError_t hipOccupancyMaxActiveBlocksPerMultiprocessor(int* n, const void*, int, size_t)
-{
-    *n = 4;
-    return hipSuccess;
-}
 }
 static void show(const char* what, long long items, int arg)
 {
@@ -96,24 +64,10 @@ ORDER_ITEM, CHOICE_ITEM = 12, 23
 
 @pytest.fixture(scope="module")
 def lines(tmp_path_factory):
-    if not os.path.exists(HIPCC):
+    if not host_driver.available():
         pytest.skip("needs hipcc")
-    tmp = tmp_path_factory.mktemp("limits")
-    drv = tmp / "driver.cpp"
-    drv.write_text(DRIVER)
-    common = [HIPCC, "-O1", "-std=c++17", "--offload-arch=gfx950", "--cuda-host-only", "-x", "hip",
-              f"-DORDER_ITEM={ORDER_ITEM}", f"-DCHOICE_ITEM={CHOICE_ITEM}",
-              "-I", os.path.join(ROOT, "include"), "-I", CSRC, "-c"]
-    objs = []
-    for src in (str(drv), os.path.join(CSRC, "radio_kernels.hip")):
-        obj = str(tmp / (os.path.basename(src) + ".o"))
-        subprocess.run(common + [src, "-o", obj], check=True, capture_output=True)
-        objs.append(obj)
-    exe = str(tmp / "driver")
-    # nothing is launched, so the kernels' code is not linked in
-    subprocess.run(["g++"] + objs + ["-Wl,--unresolved-symbols=ignore-all", "-no-pie", "-o", exe],
-                   check=True, capture_output=True)
-    out = subprocess.run([exe], check=True, capture_output=True, text=True, timeout=60).stdout
+    out = host_driver.run(tmp_path_factory.mktemp("limits"), DRIVER,
+                          (f"-DORDER_ITEM={ORDER_ITEM}", f"-DCHOICE_ITEM={CHOICE_ITEM}"))
     return [(ln.split()[0], {k: int(v) for k, v in (f.split("=") for f in ln.split()[1:])})
             for ln in out.splitlines()]
 
