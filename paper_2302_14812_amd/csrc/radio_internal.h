@@ -75,11 +75,10 @@ constexpr int kXcds = 8;                                // accelerator dies shar
 constexpr int kCounters = 4;  // a detector's device counters (DepositJob::counters)
 
 // Slots per cell in the LDS ring (the small one a power of two), 48 B per slot in every mode
-// (6 doubles, or 6 compensated single pairs).  Each tile takes the small ring
-// when the slots a batch touches fit it (four workgroups per CU), else the
-// large one (two per CU): slowly advancing arrivals, where many segments
-// share a slot, fit the small ring; arrivals that cross a slot every segment
-// or two need the large one.
+// (6 doubles).  The small ring keeps four or five workgroups on a CU, the large one
+// two: slowly advancing arrivals, where many segments share a slot, fit the small ring;
+// arrivals that cross a slot every segment or two need the large one.
+// ring_choice_kernel takes the cheaper of the two by an estimate.
 #ifndef RADIO_RING_SMALL
 #define RADIO_RING_SMALL 16
 #endif
@@ -88,12 +87,25 @@ constexpr int kCounters = 4;  // a detector's device counters (DepositJob::count
 #endif
 constexpr int kRingSmall = RADIO_RING_SMALL;
 constexpr int kRingLarge = RADIO_RING_LARGE;
-// A tile's ring choice (DepositJob::ring_sel): the small ring, or kRingSel64 + h,
-// the large one with a run staged in 2^h stretches (arrivals so sparse that a
-// longer one spans more slots than the large ring).
+// A tile's ring: the small one, or kRingSel64 + h, the large one with a run staged in
+// 2^h stretches (arrivals so sparse that a longer one spans more slots than the large
+// ring).
 constexpr int kRingSel16 = 0;
 constexpr int kRingSel64 = 1;
-constexpr int kMaxPartShift = 4;
+constexpr int kRingShifts = 5;  // h below this
+// Workspace of the ring choice, cleared by the kinematics: sums of the tiles' counts, of
+// all and of those that by themselves would take the small ring and the large one, and
+// what the last workgroup makes of them: the ring of all tiles, or kRingsOwn with the
+// large ring of those whose ring_sel is set.
+constexpr unsigned kRingsOwn = 8;
+struct RingState {
+    unsigned long long all[3 + kRingShifts], kind[2][3 + kRingShifts];
+    unsigned long long tiles[2];
+    unsigned done;
+    unsigned mode;
+};
+constexpr size_t kRingStateBytes = 256;
+static_assert(sizeof(RingState) <= kRingStateBytes, "room for the ring state");
 
 // One (detector, chunk) deposit as the kernels see it.  Sizes are 64-bit; the
 // host runtime has validated every pointer and size before filling this in.
@@ -108,7 +120,11 @@ struct DepositJob {
     const double* q;                // [n_p] or nullptr (all -1)
     void* recs;                     // workspace [n_p][n_s+1] records of the job's mode
     int32_t* perm;                  // workspace [n_groups][n_tiles][n_p]: particle orders
-    uint8_t* ring_sel;              // workspace [n_tiles]: the tiles' ring choices (kRingSel...)
+    uint8_t* ring_sel;              // workspace [n_tiles]: 1 where a tile by itself would take
+                                    // the large ring
+    RingState* rings;               // workspace: the ring choice
+    unsigned long long* rings_used; // batch: [2] set where a job uses the ring; else nullptr
+    double resident_small, resident_large;  // workgroups of this deposit the device holds at once
     const double* far;              // far-field detector: [n_c][4] n_cell, R_cell; else nullptr
     double vscale;                  // 1, or 0 for an acceleration-only detector
     int64_t hold;                   // field a segment holds: 0 current, 1 previous, 2 linear
@@ -227,10 +243,11 @@ inline int kernel_variant(int mode, const DepositJob& J)
         return (G == 0 && J.hold == 0) ? kOptionVariants + 3 * (J.shape - 1) + mode : -1;
     return mode + 3 * (G + 4 * (int)J.hold);
 }
-// next: two work counters (small-ring and large-ring workgroups)
+// next: two work counters (small-ring and large-ring workgroups), zero; used: the jobs'
+// rings_used
 hipError_t launch_deposit_batch(const DepositJob* jobs, const WorkItem* items, int64_t n_items,
-                                unsigned long long* next, int variant, int blocks_small,
-                                int blocks_large, hipStream_t s);
+                                unsigned long long* next, const unsigned long long* used,
+                                int variant, int blocks_small, int blocks_large, hipStream_t s);
 int persistent_blocks_per_cu(int variant, bool large_ring);
 hipError_t launch_readout(const double* acc, int64_t n_c, int64_t n_t, const int64_t* user_index,
                           bool pairs, double* E, double* B, hipStream_t s);

@@ -21,7 +21,8 @@
 // 3. ring_choice_kernel: per tile, whether the arrivals a batch touches fit
 //    the small LDS ring (slow advance, many segments per slot) or need the
 //    large one (a slot crossed every segment or two), with its runs staged whole
-//    or in shorter stretches; it samples batches.
+//    or in shorter stretches; it samples batches.  Where a second launch for a part
+//    of the tiles would cost more than it gains, all tiles take one ring.
 //
 // 4. deposit_kernel: one workgroup per (tile, range of runs), launched once
 //    per ring size; tiles of the other size leave at once.  Lane
@@ -851,8 +852,12 @@ __global__ __launch_bounds__(256) void kinematics_kernel(const double* __restric
                                                          int64_t n_p, int64_t n_s, int64_t stride,
                                                          int64_t s_lo, int64_t s_hi, double dt,
                                                          double inv_c, int bd_rule,
-                                                         void* __restrict__ recs_out)
+                                                         void* __restrict__ recs_out,
+                                                         RingState* __restrict__ rings)
 {
+    if (blockIdx.x == 0 && threadIdx.x == 0)
+        *rings = RingState{};  // for this deposit's ring choice
+
     using Rec = typename std::conditional<M == kModeF64, RecF64, RecMix>::type;
     Rec* recs = reinterpret_cast<Rec*>(recs_out);
     const int64_t n_states = n_s + 1;
@@ -1045,88 +1050,131 @@ __global__ __launch_bounds__(256) void order_kernel(const double* __restrict__ x
     }
 }
 
-// For every tile, the ring its batches take (DepositJob::ring_sel).  The small
-// ring keeps four or five workgroups on a CU, the large one two, so the large ring
-// pays only where the small one would send many emissions to HBM.  The kernel
-// replays sampled batches (runs spread over the chunk, places spread over the
-// tile's particle order) at the tile's first cell: it places the rings the way
-// the deposit does (below the batch's earliest start), counts the slots a lane
-// would emit outside them, and takes the cheapest by the estimates below.  The
-// large ring's runs are staged in halves, quarters, ... where a whole one would
-// outgrow it: a shorter stretch pays a batch's staging and ring move for fewer
+// The ring a deposit's tiles take (RingState::mode): the small ring keeps four or five
+// workgroups on a CU, the large one two, so the large ring pays only where the small
+// one would send many emissions to HBM.  A workgroup looks at one tile, or at a row of
+// neighbouring tiles of a large detector: it replays sampled batches (places and runs
+// by a sequence that spreads evenly over both, with another start in each workgroup;
+// with the same places and runs for every tile a sheet was taken for 0.4% outside the
+// small ring where 2.3% were) at one cell each, places the rings the way the deposit does
+// (below the batch's earliest start) and counts the slots a lane would emit outside
+// them.  The large ring's runs are staged in halves, quarters, ... where a whole one
+// would outgrow it: a shorter stretch pays a batch's staging and ring move for fewer
 // segments, and helps only where it is the run, not the spread of the batch's
-// particles, that is too long.  Only speed depends on this choice.
+// particles, that is too long.
 //
-// Estimates, in picoseconds of the whole device per interaction, E the slots a
-// run emits per segment, fitted to mixed-precision deposits (doubles cost more on
-// either side): undulator ensemble E 0.5, small ring, 2.9 ps with 0.3% outside;
-// uneven undulator sets E 0.8, 5 ps in the large ring against 18 in the small one
-// with 4% outside; plasma-mirror sheet E 1.7, 8.3 ps;
-// the sheet sampled at 6.5 slots a segment, L = 2: 34 ps, and 830 where runs of 16
-// segments outgrew the ring.
-constexpr double kSmallCost = 3.3, kSmallSlot = 1.0;  // small ring: 3.3 + 1.0 E
-// large ring, a run staged in stretches of L segments: 2.6 + 3.0 E + 15/L
-constexpr double kLargeCost = 2.6, kLargeSlot = 3.0, kLargeBatch = 15.0;
-constexpr double kOutsideSlot = 80.0;  // a slot outside the ring
-// The rings' tiles run in two launches, and a few tiles alone in the second leave
-// much of the device idle: the large ring has to gain this much (uneven sets the
-// same with 0.85 as with 1, the undulator ensemble 97 against 99.5 ms).
-constexpr double kLargeGain = 0.85;
-constexpr int kMaxRun = 16;
-static_assert(shape_run(0) <= kMaxRun && shape_run(1) <= kMaxRun && shape_run(2) <= kMaxRun,
-              "sampled runs");
+// The last workgroup to finish takes the cheapest ring by the estimates below, from
+// the counts of all tiles.  One ring for all of them: tiles of the other ring are a
+// second launch, which pays a round of its own however few they are, and a tile's own
+// samples say less than all tiles' do.  Of 50 deposits timed with either ring for all
+// tiles and with each tile's own, its own took up to 1.9 times as long as the better
+// single ring, and was the faster by 10% at the most.  Only a detector whose tiles
+// differ enough gets each tile's own: they choose by one half of their samples, and
+// what that gives is estimated from the other half, which did not choose.
+// Only speed depends on all this: emissions outside a ring go to HBM directly.
+//
+// Bound by latency: the order, then all states of a sampled run at once, which stay in
+// registers; the lanes of a batch share their minima by shuffles.  With a workgroup per
+// tile, a loop of dependent loads, LDS atomics and a step per slot crossed: 100 tiles 33
+// us, 1024 tiles 68; now 24 and 28.
 
-__global__ __launch_bounds__(256) void ring_choice_kernel(const char* __restrict__ recs,
-                                                          int64_t rec_size,
-                                                          const int32_t* __restrict__ perm,
-                                                          int64_t n_tiles, int64_t runs_per_group,
-                                                          const double* __restrict__ cells,
-                                                          const double* __restrict__ far,
-                                                          int64_t n_c, int64_t n_p, int64_t n_s,
-                                                          int64_t n_runs, double t_first,
-                                                          int64_t s0, double dt, double t0,
-                                                          double inv_dt_det, double inv_c,
-                                                          int64_t n_t, int tile_cells, int groups,
-                                                          int run_l, int max_shift,
-                                                          uint8_t* __restrict__ sel, int64_t tile0)
+// Estimates, in picoseconds of the whole device per interaction, of an average of E slots
+// emitted per segment, `out` of them outside the ring; fitted to 50 deposits a mode, each
+// timed with either ring and with stretches of 16 to one segments (undulators, sheets
+// at 0.4 to 6 slots a segment, waves, circular orbits, uneven sets; default shape, 0.1 to
+// 1.6 slots a segment):
+//   small ring  max(small + small_slot E, least + outside out): few adds to HBM hide
+//               behind the fields
+//   large ring  large + large_slot E + batch / L + missed out, L segments a stretch
+struct RingCost {
+    float small, small_slot, least, outside, large, large_slot, batch, missed;
+};
+constexpr RingCost kRingCost[3] = {
+    {4.0f, 2.0f, 1.5f, 310.0f, 4.4f, 1.7f, 22.0f, 230.0f},   // double
+    {2.6f, 2.0f, 1.0f, 310.0f, 3.4f, 1.8f, 22.0f, 230.0f},   // mixed
+    {2.7f, 2.2f, 1.0f, 720.0f, 3.6f, 2.2f, 36.0f, 350.0f}};  // compensated: two adds a
+                                                             // component, the first returning
+constexpr float kOwnGain = 0.88f;  // what each tile's own ring has to gain
+// Workgroups at most (4096 sampled batches): more add up to no better choice, and the
+// loads of their samples took 79 us for 1024 tiles.
+constexpr int64_t kChoiceBlocks = 256;
+
+// counts of a run's slots: all emitted, outside the small ring, the segments, and the
+// segments that end outside the large ring with stretches of L >> h
+struct RingCounts {
+    float all, out, segs, far[kRingShifts];
+};
+
+__device__ __forceinline__ float small_ring_cost(const RingCost& K, const RingCounts& c)
 {
-    // one thread per sampled particle: 256 / groups sampled batches
-    const int n_samples = 256 / groups;
-    // lowest slot of a sampled batch at each state of the run
-    __shared__ int start[64][kMaxRun + 1];
-    __shared__ unsigned out_count, emitted, segs, far_count[kMaxPartShift + 1];
-    const int tid = threadIdx.x;
-    const int64_t tile = tile0 + blockIdx.x;
-    const int64_t c0 = tile * tile_cells;
-    for (int i = tid; i < n_samples * (kMaxRun + 1); i += 256)
-        (&start[0][0])[i] = INT_MAX;
-    if (tid <= kMaxPartShift)
-        far_count[tid] = 0u;
-    if (tid == 0) {
-        out_count = 0u;
-        emitted = 0u;
-        segs = 0u;
+    return fmaxf(K.small + K.small_slot * c.all / c.segs, K.least + K.outside * c.out / c.segs);
+}
+
+// the cheapest stretch of runs of L segments and its cost
+__device__ __forceinline__ float large_ring_cost(const RingCost& K, const RingCounts& c, int L,
+                                                 int* shift)
+{
+    const float E = c.all / c.segs;
+    float best = INFINITY;
+    for (int h = 0; h < kRingShifts && (L >> h) > 0; ++h) {
+        const float cost = K.large + K.large_slot * E + K.batch / (float)(L >> h) +
+                           K.missed * E * c.far[h] / c.segs;
+        if (cost < best) {
+            best = cost;
+            *shift = h;
+        }
     }
-    const int smp = tid / groups;  // sampled batch
-    const int gg = tid % groups;   // particle within it
-    const int64_t n_states = n_s + 1;
-    const int64_t n_batches = (n_p + groups - 1) / groups;
-    // spread over the runs by the golden ratio, which meets no period of the motion
-    const double at = 0.6180339887498949 * (double)smp;
-    const int64_t run = min((int64_t)((at - floor(at)) * (double)n_runs), n_runs - 1);
-    const int64_t bt = (2 * (int64_t)smp + 1) * n_batches / (2 * n_samples);
+    return best;
+}
+
+template <int L>
+__global__ __launch_bounds__(256) void ring_choice_kernel(DepositJob J, int64_t rec_size,
+                                                          RingCost K, int64_t tiles_each)
+{
+    constexpr int kShifts = L == 16 ? 4 : 3;  // stretches down to one segment
+    static_assert((L >> kShifts) == 1 && kShifts < kRingShifts, "runs of 16 or 8 segments");
+    enum { kAll, kOut, kSegs, kFar, kCounts = kFar + kRingShifts };  // as RingCounts
+    __shared__ unsigned part[2][4][kCounts];  // by half of the samples
+    const int tid = threadIdx.x;
+    const int groups = J.groups;
+    const int n_samples = 256 / groups;  // sampled batches, a thread per particle
+    const int smp = tid / groups;
+    const int gg = tid % groups;
+    const int64_t tile_a = blockIdx.x * tiles_each;
+    const int64_t n_here = min(tiles_each, J.n_tiles - tile_a);
+    const int64_t tile = tile_a + (int64_t)smp * n_here / n_samples;
+    const int64_t n_batches = (J.n_p + groups - 1) / groups;
+    // runs and places: the plane sequence of the plastic number, shifted at random for
+    // each half of each workgroup's batches, which so are independent of one another
+    unsigned rnd = (blockIdx.x * 2u + (unsigned)(smp & 1) + 1u) * 0x9e3779b9u;
+    rnd = (rnd ^ (rnd >> 15)) * 0x85ebca6bu;
+    rnd = (rnd ^ (rnd >> 13)) * 0xc2b2ae35u;
+    rnd ^= rnd >> 16;
+    const double id = (double)(smp / 2);
+    const double at_run = id * 0.7548776662466927 + (double)(rnd & 0xffffu) * 0x1p-16;
+    const double at_place = id * 0.5698402909980532 + (double)(rnd >> 16) * 0x1p-16;
+    const int64_t run = min((int64_t)((at_run - floor(at_run)) * (double)J.n_runs), J.n_runs - 1);
+    const int64_t bt =
+        min((int64_t)((at_place - floor(at_place)) * (double)n_batches), n_batches - 1);
     const int64_t pi = bt * groups + gg;
-    const int64_t s_a = run * run_l;
-    const int len = (int)min((int64_t)run_l, n_s - s_a);
-    const bool on = smp < n_samples && pi < n_p && len > 0;
-    const double* xc = cells + 3 * c0;
-    const double* fc = far ? far + 4 * c0 : nullptr;
-    const int32_t* order = perm + ((run / runs_per_group) * n_tiles + tile) * n_p;  // once a thread
-    const char* pr = on ? recs + ((int64_t)order[pi] * n_states + s_a) * rec_size : nullptr;
-    // slot of state k of this lane's particle (its position: the first three
-    // doubles of its record)
-    auto slot_of = [&](int k) {
-        const double* x = reinterpret_cast<const double*>(pr + (int64_t)k * rec_size);
+    const int64_t s_a = run * L;
+    const int len = (int)min((int64_t)L, J.n_s - s_a);
+    const bool on = pi < J.n_p;
+    const int64_t c0 = tile * J.tile_cells;
+    const int64_t cell = c0 + (int64_t)(5 * smp) % min((int64_t)J.tile_cells, J.n_c - c0);
+    const double* xc = J.cells + 3 * cell;
+    const double* fc = J.far ? J.far + 4 * cell : nullptr;
+    const int32_t* order = J.perm + ((run / J.runs_per_group) * J.n_tiles + tile) * J.n_p;
+    const char* pr = reinterpret_cast<const char*>(J.recs) +
+                     ((int64_t)order[on ? pi : 0] * (J.n_s + 1) + s_a) * rec_size;
+    // slots of the run's states (a record starts with its position), and the lowest of
+    // the batch's particles at each
+    const int n_t = (int)J.n_t;
+    int slot[L + 1], start[L + 1];
+#pragma unroll
+    for (int k = 0; k <= L; ++k) {
+        const int kk = min(k, len);
+        const double* x = reinterpret_cast<const double*>(pr + kk * rec_size);
         double dist;
         if (fc) {
             dist = fc[3] - (x[0] * fc[0] + x[1] * fc[1] + x[2] * fc[2]);
@@ -1135,72 +1183,133 @@ __global__ __launch_bounds__(256) void ring_choice_kernel(const char* __restrict
             dist = __builtin_sqrt(d0 * d0 + d1 * d1 + d2 * d2);
         }
         const double u =
-            ((t_first + (double)(s0 + s_a + k) * dt) + dist * inv_c - t0) * inv_dt_det;
-        return (int)floor((u == u) ? fmin(fmax(u, -2.0), (double)n_t + 2.0) : -2.0);
+            ((J.t_first + (double)(J.s0 + s_a + kk) * J.dt) + dist * J.inv_c - J.t0) * J.inv_dt_det;
+        slot[k] = (int)floor((u == u) ? fmin(fmax(u, -2.0), (double)n_t + 2.0) : -2.0);
+        start[k] = on ? slot[k] : INT_MAX;
+    }
+    for (int m = groups / 2; m > 0; m >>= 1)
+#pragma unroll
+        for (int k = 0; k < L; ++k)
+            start[k] = min(start[k], __shfl_xor(start[k], m));
+    // where a ring of R slots starts that is placed at a batch's lowest slot
+    auto placed = [&](int lo, int R) { return min(max(lo - kRingMargin, 0), max(n_t - R, 0)); };
+    unsigned count[kCounts] = {};
+    const int base = placed(start[0], kRingSmall);
+    // slots [a, b) left: all within the window, and those outside the small ring
+    auto emit = [&](int a, int b) {
+        const int all = max(min(b, n_t) - max(a, 0), 0);
+        const int in = max(min(min(b, n_t), base + kRingSmall) - max(a, base), 0);
+        count[kAll] += (unsigned)all;
+        count[kOut] += (unsigned)(all - in);
     };
-    __syncthreads();
-    if (on)
-        for (int k = 0; k <= len; ++k)
-            atomicMin(&start[smp][k], slot_of(k));
-    __syncthreads();
+    int base_large[kShifts + 1];
+#pragma unroll
+    for (int k = 1; k <= L; ++k) {
+        const int prev = slot[k - 1], cur = slot[k];
+        if (on && k <= len)
+            emit(min(prev, cur), max(prev, cur));
+#pragma unroll
+        for (int h = 0; h <= kShifts; ++h) {  // the large ring, by length of stretch
+            if (((k - 1) & ((L >> h) - 1)) == 0)
+                base_large[h] = placed(start[k - 1], kRingLarge);
+            count[kFar + h] += on && k <= len && cur >= 0 && cur < n_t &&
+                                       (cur < base_large[h] || cur >= base_large[h] + kRingLarge)
+                                   ? 1u
+                                   : 0u;
+        }
+    }
     if (on) {
-        // where a ring of R slots starts that is placed at state k
-        auto base_at = [&](int k, int R) {
-            return (int)fmin(fmax((double)start[smp][k] - (double)kRingMargin, 0.0),
-                             fmax((double)(n_t - R), 0.0));
-        };
-        const int base = base_at(0, kRingSmall);
-        unsigned outside = 0u, all = 0u, far_segs[kMaxPartShift + 1] = {};
-        auto emit = [&](int j) {
-            if (j >= 0 && j < n_t) {
-                ++all;
-                outside += (j < base || j >= base + kRingSmall) ? 1u : 0u;
-            }
-        };
-        int J = slot_of(0);
-        for (int k = 1; k <= len; ++k) {
-            const int jk = slot_of(k);
-            for (int j = min(J, jk); j < max(J, jk); ++j)  // slots the lane leaves
-                emit(j);
+        emit(slot[L], slot[L] + 1);  // the run's last slot
+        count[kSegs] = (unsigned)len;
+    }
 #pragma unroll
-            for (int h = 0; h <= kMaxPartShift; ++h)  // the large ring, by length of stretch
-                if (h <= max_shift && jk >= 0 && jk < n_t) {
-                    const int part = max(run_l >> h, 1);
-                    const int b = base_at((k - 1) / part * part, kRingLarge);
-                    far_segs[h] += (jk < b || jk >= b + kRingLarge) ? 1u : 0u;
-                }
-            J = jk;
-        }
-        emit(J);  // the run's last slot
-        atomicAdd(&out_count, outside);
-        atomicAdd(&emitted, all);
-        atomicAdd(&segs, (unsigned)len);
-#pragma unroll
-        for (int h = 0; h <= kMaxPartShift; ++h)
-            if (far_segs[h])
-                atomicAdd(&far_count[h], far_segs[h]);
+    for (int i = 0; i < kCounts; ++i) {
+        for (int m = 32; m > 0; m >>= 1)
+            if (m != groups)  // the even and the odd batches each for themselves
+                count[i] += __shfl_xor(count[i], m);
+        if ((tid % 64 & ~groups) == 0)
+            part[(tid % 64) / groups][tid / 64][i] = count[i];
     }
     __syncthreads();
-    if (tid == 0) {
-        int choice = kRingSel16;
-        if (segs > 0u) {
-            const double n = (double)segs;
-            const double E = (double)emitted / n;
-            double best =
-                kLargeGain * (kSmallCost + kSmallSlot * E + kOutsideSlot * (double)out_count / n);
-            for (int h = 0; h <= max_shift; ++h) {
-                const double stretch = (double)max(run_l >> h, 1);
-                const double missed = E * (double)far_count[h] / n;
-                const double cost = kLargeCost + kLargeSlot * E + kLargeBatch / stretch +
-                                    kOutsideSlot * missed;
-                if (cost < best) {
-                    best = cost;
-                    choice = kRingSel64 + h;
-                }
-            }
-        }
-        sel[tile] = (uint8_t)choice;
+    if (tid >= 64)
+        return;
+    // every lane of the first wavefront: which ring the tiles by themselves would take
+    auto of_half = [&](int half, int i) {
+        return part[half][0][i] + part[half][1][i] + part[half][2][i] + part[half][3][i];
+    };
+    RingCounts c;
+#pragma unroll
+    for (int i = 0; i < kCounts; ++i)
+        (&c.all)[i] = (float)of_half(0, i);
+    int shift = 0;
+    const int own = large_ring_cost(K, c, L, &shift) < small_ring_cost(K, c) ? 1 : 0;
+    for (int64_t i = tid; i < n_here; i += 64)
+        J.ring_sel[tile_a + i] = (uint8_t)own;
+    // the sums of all, and by the other half of either kind of tile; the last workgroup
+    // settles the mode
+    RingState* R = J.rings;
+    auto add = [&](unsigned long long* to, int64_t v) {
+        __hip_atomic_fetch_add(to, (unsigned long long)v, __ATOMIC_RELAXED,
+                               __HIP_MEMORY_SCOPE_AGENT);
+    };
+    if (tid < kCounts) {
+        add(&R->all[tid], of_half(0, tid) + of_half(1, tid));
+        add(&R->kind[own][tid], of_half(1, tid));
+    } else if (tid == kCounts) {
+        add(&R->tiles[own], n_here);
     }
+    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "agent");  // the wavefront's adds, before `done`
+    if (tid != 0)
+        return;
+    const unsigned done =
+        __hip_atomic_fetch_add(&R->done, 1u, __ATOMIC_ACQ_REL, __HIP_MEMORY_SCOPE_AGENT);
+    if (done + 1u != gridDim.x)
+        return;
+    auto get = [&](unsigned long long* from) {
+        return (float)__hip_atomic_load(from, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    };
+    RingCounts kind[2], all;
+    for (int i = 0; i < kCounts; ++i) {
+        (&kind[0].all)[i] = get(&R->kind[0][i]);
+        (&kind[1].all)[i] = get(&R->kind[1][i]);
+        (&all.all)[i] = get(&R->all[i]);
+    }
+    const float n[2] = {get(&R->tiles[0]), get(&R->tiles[1])};
+    const float items = (float)(J.n_splits * J.n_parts);  // of a tile
+    // time of a launch over n tiles of the cost: its rounds of resident workgroups, at
+    // least one
+    auto launch = [&](float tiles, float cost, double resident) {
+        return cost * fmaxf(tiles, (float)resident / items);
+    };
+    int shift_own = 0;
+    const float small = launch(n[0] + n[1], small_ring_cost(K, all), J.resident_small);
+    const float large =
+        launch(n[0] + n[1], large_ring_cost(K, all, L, &shift), J.resident_large);
+    unsigned mode = small <= large ? kRingSel16 : kRingSel64 + shift;
+    if (kind[0].segs > 0.0f && kind[1].segs > 0.0f) {
+        const float mixed = launch(n[0], small_ring_cost(K, kind[0]), J.resident_small) +
+                            launch(n[1], large_ring_cost(K, kind[1], L, &shift_own),
+                                   J.resident_large);
+        if (mixed < kOwnGain * fminf(small, large))
+            mode = kRingsOwn | (kRingSel64 + shift_own);
+    }
+    R->mode = mode;
+    if (J.rings_used) {  // a batch: which of its launches has work
+        if (mode == kRingSel16 || (mode & kRingsOwn))
+            __hip_atomic_fetch_or(J.rings_used, 1ull, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        if (mode != kRingSel16)
+            __hip_atomic_fetch_or(J.rings_used + 1, 1ull, __ATOMIC_RELAXED,
+                                  __HIP_MEMORY_SCOPE_AGENT);
+    }
+}
+
+// The ring of a tile (kRingSel...)
+__device__ __forceinline__ int ring_of(const DepositJob& J, int64_t tile)
+{
+    const unsigned mode = gptr(J.rings)->mode;
+    if ((mode & kRingsOwn) == 0)
+        return (int)mode;
+    return gptr(J.ring_sel)[tile] != 0 ? (int)(mode & ~kRingsOwn) : kRingSel16;
 }
 
 // M: arithmetic of the deposit (field in double or single; accumulation in
@@ -1819,7 +1928,7 @@ __attribute__((amdgpu_waves_per_eu(kMinWaves<M, R, G, HOLD, SH>))) void deposit_
     if (logical >= J.n_tiles * J.n_splits * J.n_parts)
         return;
     const int64_t tile = logical % J.n_tiles;
-    const int sel = gptr(J.ring_sel)[tile];
+    const int sel = ring_of(J, tile);
     if ((sel != kRingSel16) != (R == kRingLarge))
         return;
     const int64_t rest = logical / J.n_tiles;  // split-major, then part
@@ -1846,8 +1955,10 @@ __global__ __launch_bounds__(kDepositThreads)
 __attribute__((amdgpu_waves_per_eu(kPersistentWaves<M, R, G, HOLD, SH>))) void
 deposit_persistent_kernel(
     const DepositJob* __restrict__ jobs, const WorkItem* __restrict__ items, int64_t n_items,
-    unsigned long long* __restrict__ next)
+    unsigned long long* __restrict__ next, const unsigned long long* __restrict__ used)
 {
+    if (gptr(used)[R == kRingLarge ? 1 : 0] == 0)
+        return;  // no job has a tile for this ring: each item would be claimed only to be left
     __shared__ __align__(16) DepositShared<M, R, SH> sh;
     __shared__ int64_t cur;
     for (;;) {
@@ -1860,7 +1971,7 @@ deposit_persistent_kernel(
             break;
         const WorkItem w = items[it];
         const DepositJob J = jobs[w.job];
-        const int sel = gptr(J.ring_sel)[w.tile];
+        const int sel = ring_of(J, w.tile);
         if ((sel != kRingSel16) != (R == kRingLarge))
             continue;
         deposit_item_of<M, R, G, HOLD, SH>(J, w.tile, w.split, w.part, sel, sh);
@@ -2208,11 +2319,11 @@ hipError_t launch_kinematics(const DepositJob& job, int mode, hipStream_t s)
     if (mode == kModeF64)
         hipLaunchKernelGGL(kinematics_kernel<kModeF64>, dim3((unsigned)blocks), dim3(256), 0, s,
                            job.x, job.u, job.q, job.n_p, job.n_s, job.xs_stride, -job.s_before,
-                           job.n_s + job.s_after, job.dt, job.inv_c, rule, job.recs);
+                           job.n_s + job.s_after, job.dt, job.inv_c, rule, job.recs, job.rings);
     else
         hipLaunchKernelGGL(kinematics_kernel<kModeMix>, dim3((unsigned)blocks), dim3(256), 0, s,
                            job.x, job.u, job.q, job.n_p, job.n_s, job.xs_stride, -job.s_before,
-                           job.n_s + job.s_after, job.dt, job.inv_c, rule, job.recs);
+                           job.n_s + job.s_after, job.dt, job.inv_c, rule, job.recs, job.rings);
     return hipGetLastError();
 }
 
@@ -2232,18 +2343,13 @@ hipError_t launch_order(const DepositJob& job, hipStream_t s)
 
 hipError_t launch_ring_choice(const DepositJob& job, int mode, hipStream_t s)
 {
-    int max_shift = 0;  // stretches down to one segment
-    while (max_shift < kMaxPartShift && (job.run_l >> (max_shift + 1)) > 0)
-        ++max_shift;
-    for (int64_t tile0 = 0; tile0 < job.n_tiles; tile0 += kMaxDepositGrid)
-        hipLaunchKernelGGL(ring_choice_kernel,
-                           dim3((unsigned)std::min<int64_t>(job.n_tiles - tile0, kMaxDepositGrid)),
-                           dim3(256), 0, s, reinterpret_cast<const char*>(job.recs),
-                           (int64_t)rec_bytes(mode), job.perm, job.n_tiles, job.runs_per_group,
-                           job.cells, job.far, job.n_c, job.n_p, job.n_s, job.n_runs, job.t_first,
-                           job.s0, job.dt, job.t0, job.inv_dt_det, job.inv_c, job.n_t,
-                           (int)job.tile_cells, (int)job.groups, (int)job.run_l, max_shift,
-                           job.ring_sel, tile0);
+    if (job.n_tiles <= 0)
+        return hipSuccess;
+    const int64_t each = (job.n_tiles + kChoiceBlocks - 1) / kChoiceBlocks;
+    const dim3 grid((unsigned)((job.n_tiles + each - 1) / each));
+    auto kernel = job.run_l == 16 ? ring_choice_kernel<16> : ring_choice_kernel<8>;
+    hipLaunchKernelGGL(kernel, grid, dim3(256), 0, s, job, (int64_t)rec_bytes(mode),
+                       kRingCost[mode], each);
     return hipGetLastError();
 }
 
@@ -2275,16 +2381,17 @@ static void launch_deposit_index(const DepositJob& job, dim3 grid, hipStream_t s
 
 template <int V>
 static void launch_persistent_index(const DepositJob* jobs, const WorkItem* items,
-                                    int64_t n_items, unsigned long long* next, int blocks_small,
+                                    int64_t n_items, unsigned long long* next,
+                                    const unsigned long long* used, int blocks_small,
                                     int blocks_large, hipStream_t s)
 {
     using K = VariantOf<V>;
     hipLaunchKernelGGL((deposit_persistent_kernel<K::M, kRingSmall, K::G, K::HOLD, K::SH>),
                        dim3((unsigned)blocks_small), dim3(kDepositThreads), 0, s, jobs, items,
-                       n_items, next);
+                       n_items, next, used);
     hipLaunchKernelGGL((deposit_persistent_kernel<K::M, kRingLarge, K::G, K::HOLD, K::SH>),
                        dim3((unsigned)blocks_large), dim3(kDepositThreads), 0, s, jobs, items,
-                       n_items, next + 1);
+                       n_items, next + 1, used);
 }
 
 template <int V>
@@ -2306,7 +2413,7 @@ template <int... V>
 struct VariantTable {
     using Single = void (*)(const DepositJob&, dim3, hipStream_t);
     using Launch = void (*)(const DepositJob*, const WorkItem*, int64_t, unsigned long long*,
-                            int, int, hipStream_t);
+                            const unsigned long long*, int, int, hipStream_t);
     using Occ = int (*)(bool);
     static constexpr Single single[] = {&launch_deposit_index<V>...};
     static constexpr Launch launch[] = {&launch_persistent_index<V>...};
@@ -2370,17 +2477,14 @@ hipError_t launch_few(const DepositJob& job, int mode, int64_t n_cus, hipStream_
 }
 
 hipError_t launch_deposit_batch(const DepositJob* jobs, const WorkItem* items, int64_t n_items,
-                                unsigned long long* next, int variant, int blocks_small,
-                                int blocks_large, hipStream_t s)
+                                unsigned long long* next, const unsigned long long* used,
+                                int variant, int blocks_small, int blocks_large, hipStream_t s)
 {
     if (n_items <= 0)
         return hipSuccess;
     if (variant < 0 || variant >= kKernelVariants)
         return hipErrorInvalidValue;
-    hipError_t e = launch_zero_u64(next, 2, s);
-    if (e != hipSuccess)
-        return e;
-    Variants::launch[variant](jobs, items, n_items, next, blocks_small, blocks_large, s);
+    Variants::launch[variant](jobs, items, n_items, next, used, blocks_small, blocks_large, s);
     return hipGetLastError();
 }
 

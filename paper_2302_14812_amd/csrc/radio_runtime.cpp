@@ -35,7 +35,7 @@ struct radio_detector {
     size_t recs_cap = 0;                       // in bytes
     int32_t* d_perm = nullptr;                 // workspace, grown on demand
     size_t perm_cap = 0;                       // in entries
-    uint8_t* d_sel = nullptr;                  // workspace: ring size per tile
+    uint8_t* d_sel = nullptr;                  // workspace: ring state, ring size per tile
     size_t sel_cap = 0;
     int32_t options = 0;                       // RADIO_FAR_FIELD | RADIO_ACCEL_ONLY
     double* d_far = nullptr;                   // FAR_FIELD: [n_c][4] n_cell, R_cell per row
@@ -330,8 +330,10 @@ radio::DepositJob make_job(const radio_detector* det, const radio_chunk* k)
     // other shapes are compiled for those only)
     const int shape = current_tuning().shape;
     radio::set_shape(J, (det->options == 0 && shape > 0 && shape < radio::kShapes) ? shape : 0);
-    const int per_cu =
-        radio::persistent_blocks_per_cu(radio::kernel_variant(det->precision, J), false);
+    const int variant = radio::kernel_variant(det->precision, J);
+    const int per_cu = radio::persistent_blocks_per_cu(variant, false);
+    J.resident_small = (double)det->n_cus * (double)per_cu;
+    J.resident_large = (double)det->n_cus * (double)radio::persistent_blocks_per_cu(variant, true);
     radio::plan_job(J, current_tuning().target_blocks, (int64_t)det->n_cus * per_cu);
     radio::set_groups(J, radio::max_order_groups(J, radio::rec_bytes(det->precision),
                                                  current_tuning().order_budget_mib));
@@ -437,7 +439,7 @@ int reserve(radio_detector* det, const radio::DepositJob& J, hipStream_t s)
     if (rc == RADIO_OK)
         rc = grow(&det->d_perm, &det->perm_cap, (size_t)(J.n_groups * J.n_tiles * J.n_p), s);
     if (rc == RADIO_OK)
-        rc = grow(&det->d_sel, &det->sel_cap, (size_t)J.n_tiles, s);
+        rc = grow(&det->d_sel, &det->sel_cap, radio::kRingStateBytes + (size_t)J.n_tiles, s);
     return rc;
 }
 
@@ -469,7 +471,8 @@ int enqueue_deposit(radio_detector* det, const radio_chunk* k, hipStream_t s)
             return rc;
         J.recs = det->d_recs;
         J.perm = det->d_perm;
-        J.ring_sel = det->d_sel;
+        J.rings = reinterpret_cast<radio::RingState*>(det->d_sel);
+        J.ring_sel = det->d_sel + radio::kRingStateBytes;
         if (radio::launch_kinematics(J, det->precision, s) != hipSuccess ||
             radio::launch_order(J, s) != hipSuccess ||
             radio::launch_ring_choice(J, det->precision, s) != hipSuccess ||
@@ -491,7 +494,8 @@ int enqueue_deposit(radio_detector* det, const radio_chunk* k, hipStream_t s)
 // ---------------------------------------------------------------------------
 constexpr size_t kScratchBytes = size_t(256) << 20;
 constexpr int kMaxDevices = 64;
-static __device__ __align__(256) unsigned char scratch[kScratchBytes];
+// (past what a chunk may take: the ring state)
+static __device__ __align__(256) unsigned char scratch[kScratchBytes + radio::kRingStateBytes];
 std::mutex g_scratch_mu;
 char* g_scratch_ptr[kMaxDevices] = {};
 
@@ -569,6 +573,7 @@ int enqueue_deposit_noalloc(radio_detector* det, const radio_chunk* k, hipStream
         J.recs = base;
         J.perm = reinterpret_cast<int32_t*>(base + rec_b);
         J.ring_sel = reinterpret_cast<uint8_t*>(base + rec_b + perm_b);
+        J.rings = reinterpret_cast<radio::RingState*>(base + kScratchBytes);
         if (radio::launch_kinematics(J, det->precision, s) != hipSuccess ||
             radio::launch_order(J, s) != hipSuccess ||
             radio::launch_ring_choice(J, det->precision, s) != hipSuccess ||
@@ -589,12 +594,14 @@ struct BatchArena {
     size_t jobs_cap = 0;
     radio::WorkItem* d_items = nullptr;
     size_t items_cap = 0;
-    unsigned long long* d_next = nullptr;  // two counters (ring sizes) per kernel variant
+    // per kernel variant two work counters (ring sizes), then two words that say whether
+    // any job uses the ring
+    unsigned long long* d_next = nullptr;
     char* d_recs = nullptr;  // state records of every pair, in bytes
     size_t recs_cap = 0;
     int32_t* d_perm = nullptr;
     size_t perm_cap = 0;
-    uint8_t* d_sel = nullptr;
+    uint8_t* d_sel = nullptr;  // the pairs' ring states, then their ring choices
     size_t sel_cap = 0;
     hipEvent_t done = nullptr;
     bool pending = false;
@@ -626,7 +633,7 @@ int enqueue_batch(radio_detector* const* dets, const radio_chunk* chunks, int n,
         hipDeviceProp_t prop;
         if (hipGetDeviceProperties(&prop, dev) != hipSuccess ||
             hipEventCreateWithFlags(&A->done, hipEventDisableTiming) != hipSuccess ||
-            hipMalloc((void**)&A->d_next, 2 * kVariants * sizeof(unsigned long long)) != hipSuccess) {
+            hipMalloc((void**)&A->d_next, 4 * kVariants * sizeof(unsigned long long)) != hipSuccess) {
             (void)hipGetLastError();
             return RADIO_EDEVICE;
         }
@@ -665,7 +672,7 @@ int enqueue_batch(radio_detector* const* dets, const radio_chunk* chunks, int n,
         const radio::DepositJob& J = P.W;
         recs_need += (size_t)(J.n_p * (J.n_s + 1)) * radio::rec_bytes(dets[i]->precision);
         perm_need += (size_t)(J.n_groups * J.n_tiles * J.n_p);
-        sel_need += (size_t)J.n_tiles;
+        sel_need += radio::kRingStateBytes + (size_t)J.n_tiles;
         A->h_jobs.push_back(J);
         idx.push_back(i);
     }
@@ -720,21 +727,33 @@ int enqueue_batch(radio_detector* const* dets, const radio_chunk* chunks, int n,
     // plan_job cuts a single deposit (electrons in a plane
     // wave, 8699 x 16 steps x 97 x 67 cells, double: 15.7 -> 5.8 ms)
     const int64_t parts = std::max<int64_t>(1, (int64_t)std::ceil(2.0 * resident / (double)n_items));
+    n_items = 0;
+    for (radio::DepositJob& J : A->h_jobs) {
+        radio::set_parts(J, std::min<int64_t>(parts, ((J.n_p + J.groups - 1) / J.groups) / 4));
+        n_items += J.n_splits * J.n_tiles * J.n_parts;
+    }
+    unsigned long long* const used = A->d_next + 2 * kVariants;
+    if (radio::launch_zero_u64(A->d_next, 4 * kVariants, s) != hipSuccess)
+        return RADIO_EDEVICE;
     std::vector<Item> items;
-    size_t ro = 0, po = 0, so = 0;
+    size_t ro = 0, po = 0, so = radio::kRingStateBytes * A->h_jobs.size();
     for (size_t j = 0; j < A->h_jobs.size(); ++j) {
         radio::DepositJob& J = A->h_jobs[j];
         const int prec = dets[idx[j]]->precision;
         J.recs = A->d_recs + ro;
         J.perm = A->d_perm + po;
+        J.rings = reinterpret_cast<radio::RingState*>(A->d_sel + radio::kRingStateBytes * j);
         J.ring_sel = A->d_sel + so;
         ro += (size_t)(J.n_p * (J.n_s + 1)) * radio::rec_bytes(prec);
         po += (size_t)(J.n_groups * J.n_tiles * J.n_p);
         so += (size_t)J.n_tiles;
         const double run_work = (double)J.tile_cells * (double)J.n_p * (double)J.run_l;
-        const int64_t n_batches = (J.n_p + J.groups - 1) / J.groups;
-        radio::set_parts(J, std::min<int64_t>(parts, n_batches / 4));
         const int mode = radio::kernel_variant(prec, J);  // kernel variant
+        J.rings_used = used + 2 * mode;
+        // its share of the device
+        const double share = (double)(J.n_splits * J.n_tiles * J.n_parts) / (double)n_items;
+        J.resident_small *= share;
+        J.resident_large *= share;
         for (int64_t sp = 0; sp < J.n_splits; ++sp) {
             const int64_t runs = std::min<int64_t>(J.runs_per_split, J.n_runs - sp * J.runs_per_split);
             for (int64_t t = 0; t < J.n_tiles; ++t)
@@ -768,7 +787,7 @@ int enqueue_batch(radio_detector* const* dets, const radio_chunk* chunks, int n,
         while (e < items.size() && items[e].mode == mode)
             ++e;
         if (radio::launch_deposit_batch(A->d_jobs, A->d_items + b, (int64_t)(e - b),
-                                        A->d_next + 2 * mode, mode, A->n_cus * bpc[mode][0],
+                                        A->d_next + 2 * mode, used + 2 * mode, mode, A->n_cus * bpc[mode][0],
                                         A->n_cus * bpc[mode][1], s) != hipSuccess)
             return RADIO_EDEVICE;
         b = e;

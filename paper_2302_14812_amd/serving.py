@@ -433,6 +433,7 @@ def _shape_minima():
 
 
 (_TILE_CELLS, _RUN_L), _RUNS_PER_ORDER, _REC_BYTES = _shape_minima(), 2, 80
+_RING_STATE_BYTES = 256  # beside the ring choices
 
 
 def workspace_bytes(spec, piece_work: float) -> int:
@@ -448,7 +449,7 @@ def workspace_bytes(spec, piece_work: float) -> int:
     tiles = -(-n_c // _TILE_CELLS)
     states = _RUNS_PER_ORDER * _RUN_L + 1
     n_p = int(math.ceil(piece_work / (float(states) * n_c)))
-    return tiles * n_p * 4 + n_p * states * _REC_BYTES + tiles
+    return tiles * n_p * 4 + n_p * states * _REC_BYTES + tiles + _RING_STATE_BYTES
 
 
 def resident_bytes(spec, piece_work: float) -> int:
