@@ -214,7 +214,7 @@ hipError_t launch_deposit(const DepositJob& job, int mode, int64_t max_grid, hip
 // jobs of at most kFewParticles particles with the default geometry and hold.  Its
 // time grows with the particles (1e11 interactions/s, less where slots are many),
 // that of the general kernels, whose batch takes 16, hardly does, but it grows with
-// the slots a step crosses and has four launches.  So from kFewAlways on, much work
+// the slots a step crosses and has four launches.  So beyond kFewAlways, much work
 // at dense arrivals, which merge in the rings (slots of kFewDense steps or more, or
 // kFewCrowded steps and more to a slot of the window), takes the general kernels.  Circular orbits, double, few against general: 800 steps x 128
 // x 128 cells x 64 slots 405 against 503 us with 3 particles, 535 against 508 with 4,
@@ -227,7 +227,7 @@ constexpr int64_t kFewParticles = 6;
 constexpr int64_t kFewAlways = 3;
 constexpr double kFewDense = 2.0;  // slot width in steps
 constexpr int64_t kFewCrowded = 8;  // steps per slot of the window
-constexpr double kFewWork = 1.0e7;  // interactions
+constexpr double kFewWork[kFewParticles - kFewAlways] = {5.0e7, 2.0e7, 1.0e7};  // interactions
 constexpr int64_t kFewCells = 8;  // cells a wavefront takes at most
 bool few_particles(const DepositJob& job);
 hipError_t launch_few(const DepositJob& job, int mode, int64_t n_cus, hipStream_t s);

@@ -2454,7 +2454,8 @@ bool few_particles(const DepositJob& job)
     // dense: slots of several steps, or more segments than the window's slots can take
     const bool dense = job.dt_det >= kFewDense * job.dt || job.n_s >= kFewCrowded * job.n_t;
     return job.n_p <= kFewAlways || !dense ||
-           (double)job.n_p * (double)job.n_s * (double)job.n_c <= kFewWork;
+           (double)job.n_p * (double)job.n_s * (double)job.n_c <=
+               kFewWork[job.n_p - kFewAlways - 1];
 }
 
 hipError_t launch_few(const DepositJob& job, int mode, int64_t n_cus, hipStream_t s)

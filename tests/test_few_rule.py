@@ -24,6 +24,7 @@ int main()
         {6, 800, 1024, 12, 0, 0, 0, 64},
         {6, 2000, 16384, 0.1, 0, 0, 0, 1000},
         {6, 1, 262144, 12, 0, 0, 0, 64},
+        {4, 3000, 4096, 12, 0, 0, 0, 128}, {5, 800, 4096, 12, 0, 0, 0, 64},
         {4, 800, 16384, 12, 0, 0, 0, 64},
         {6, 800, 16384, 12, 0, 0, 0, 4096},
         {5, 200, 65536, 2, 0, 0, 0, 128},
@@ -49,4 +50,4 @@ int main()
 
 @pytest.mark.skipif(not host_driver.available(), reason="needs hipcc")
 def test_few_rule(tmp_path):
-    assert host_driver.run(tmp_path, 'extern "C"' + DRIVER).strip() == "111111" + "0" * 9
+    assert host_driver.run(tmp_path, 'extern "C"' + DRIVER).strip() == "11111111" + "0" * 9
