@@ -93,13 +93,13 @@ constexpr int kRingLarge = RADIO_RING_LARGE;
 constexpr int kRingSel16 = 0;
 constexpr int kRingSel64 = 1;
 constexpr int kRingShifts = 5;  // h below this
-// Workspace of the ring choice, cleared by the kinematics: sums of the tiles' counts, of
-// all and of those that by themselves would take the small ring and the large one, and
-// what the last workgroup makes of them: the ring of all tiles, or kRingsOwn with the
-// large ring of those whose ring_sel is set.
+// Workspace of the ring choice, cleared by the kinematics: sums of the counts of the
+// tiles that by themselves would take the small ring and of those that would take the
+// large one, and what the last workgroup makes of them: the ring of all tiles, or
+// kRingsOwn with the large ring of those whose ring_sel is set.
 constexpr unsigned kRingsOwn = 8;
 struct RingState {
-    unsigned long long all[3 + kRingShifts], kind[2][3 + kRingShifts];
+    unsigned long long kind[2][3 + kRingShifts];
     unsigned long long tiles[2];
     unsigned done;
     unsigned mode;
@@ -219,7 +219,8 @@ hipError_t launch_deposit(const DepositJob& job, int mode, int64_t max_grid, hip
 // kFewCrowded steps and more to a slot of the window), takes the general kernels.  Circular orbits, double, few against general: 800 steps x 128
 // x 128 cells x 64 slots 405 against 503 us with 3 particles, 535 against 508 with 4,
 // 792 against 664 with 6 (mixed 383 against 537, 507 against 542, 753 against 606);
-// 800 x 32 x 32 cells with 6 79 against 95; an undulator's 2000 steps x 64 x 64 cells
+// 3000 x 64 x 64 cells x 128 slots with 4 483 against 644, 800 x 64 x 64 with 5 196
+// against 237, with 6 234 against 240 (mixed 221 against 186); an undulator's 2000 steps x 64 x 64 cells
 // x 1000 slots with 6 595 against 2070, 500 x 128 x 128 cells x 32 slots with 6 475
 // against 406; one step x 512 x 512 cells with 6 850 against
 // 920.

@@ -1054,9 +1054,9 @@ __global__ __launch_bounds__(256) void order_kernel(const double* __restrict__ x
 // workgroups on a CU, the large one two, so the large ring pays only where the small
 // one would send many emissions to HBM.  A workgroup looks at one tile, or at a row of
 // neighbouring tiles of a large detector: it replays sampled batches (places and runs
-// by a sequence that spreads evenly over both, with another start in each workgroup;
-// with the same places and runs for every tile a sheet was taken for 0.4% outside the
-// small ring where 2.3% were) at one cell each, places the rings the way the deposit does
+// by a sequence that spreads evenly over both, for the estimates with another start in
+// each workgroup; with the same places and runs everywhere a sheet was taken for 0.4%
+// outside the small ring where 2.3% were) at one cell each, places the rings the way the deposit does
 // (below the batch's earliest start) and counts the slots a lane would emit outside
 // them.  The large ring's runs are staged in halves, quarters, ... where a whole one
 // would outgrow it: a shorter stretch pays a batch's staging and ring move for fewer
@@ -1069,8 +1069,9 @@ __global__ __launch_bounds__(256) void order_kernel(const double* __restrict__ x
 // samples say less than all tiles' do.  Of 50 deposits timed with either ring for all
 // tiles and with each tile's own, its own took up to 1.9 times as long as the better
 // single ring, and was the faster by 10% at the most.  Only a detector whose tiles
-// differ enough gets each tile's own: they choose by one half of their samples, and
-// what that gives is estimated from the other half, which did not choose.
+// differ enough gets each tile's own: they choose by one half of their samples, the same
+// places and runs for all, so that it is the tiles that differ, and what either way
+// costs is estimated from the other half.
 // Only speed depends on all this: emissions outside a ring go to HBM directly.
 //
 // Bound by latency: the order, then all states of a sampled run at once, which stay in
@@ -1094,7 +1095,11 @@ constexpr RingCost kRingCost[3] = {
     {2.6f, 2.0f, 1.0f, 310.0f, 3.4f, 1.8f, 22.0f, 230.0f},   // mixed
     {2.7f, 2.2f, 1.0f, 720.0f, 3.6f, 2.2f, 36.0f, 350.0f}};  // compensated: two adds a
                                                              // component, the first returning
-constexpr float kOwnGain = 0.88f;  // what each tile's own ring has to gain
+// what each tile's own ring has to gain: in a batch the other pairs fill its launches
+constexpr float kOwnGain = 0.88f, kOwnGainBatch = 0.96f;
+// a round's time with one workgroup a CU, of that with all that are resident (200 electrons
+// x 200 steps x 16 x 16 cells, 624 items: 124 us in the small ring, 158 in the large one)
+constexpr float kAloneSmall = 0.4f, kAloneLarge = 0.7f;
 // Workgroups at most (4096 sampled batches): more add up to no better choice, and the
 // loads of their samples took 79 us for 1024 tiles.
 constexpr int64_t kChoiceBlocks = 256;
@@ -1144,9 +1149,9 @@ __global__ __launch_bounds__(256) void ring_choice_kernel(DepositJob J, int64_t 
     const int64_t n_here = min(tiles_each, J.n_tiles - tile_a);
     const int64_t tile = tile_a + (int64_t)smp * n_here / n_samples;
     const int64_t n_batches = (J.n_p + groups - 1) / groups;
-    // runs and places: the plane sequence of the plastic number, shifted at random for
-    // each half of each workgroup's batches, which so are independent of one another
-    unsigned rnd = (blockIdx.x * 2u + (unsigned)(smp & 1) + 1u) * 0x9e3779b9u;
+    // runs and places: the plane sequence of the plastic number, the same for one half of
+    // each workgroup's batches, shifted at random from workgroup to workgroup for the other
+    unsigned rnd = (smp & 1 ? blockIdx.x + 1u : 0u) * 0x9e3779b9u;
     rnd = (rnd ^ (rnd >> 15)) * 0x85ebca6bu;
     rnd = (rnd ^ (rnd >> 13)) * 0xc2b2ae35u;
     rnd ^= rnd >> 16;
@@ -1245,15 +1250,14 @@ __global__ __launch_bounds__(256) void ring_choice_kernel(DepositJob J, int64_t 
     const int own = large_ring_cost(K, c, L, &shift) < small_ring_cost(K, c) ? 1 : 0;
     for (int64_t i = tid; i < n_here; i += 64)
         J.ring_sel[tile_a + i] = (uint8_t)own;
-    // the sums of all, and by the other half of either kind of tile; the last workgroup
-    // settles the mode
+    // by the other half, the sums of either kind of tile; the last workgroup settles the
+    // mode
     RingState* R = J.rings;
     auto add = [&](unsigned long long* to, int64_t v) {
         __hip_atomic_fetch_add(to, (unsigned long long)v, __ATOMIC_RELAXED,
                                __HIP_MEMORY_SCOPE_AGENT);
     };
     if (tid < kCounts) {
-        add(&R->all[tid], of_half(0, tid) + of_half(1, tid));
         add(&R->kind[own][tid], of_half(1, tid));
     } else if (tid == kCounts) {
         add(&R->tiles[own], n_here);
@@ -1272,25 +1276,28 @@ __global__ __launch_bounds__(256) void ring_choice_kernel(DepositJob J, int64_t 
     for (int i = 0; i < kCounts; ++i) {
         (&kind[0].all)[i] = get(&R->kind[0][i]);
         (&kind[1].all)[i] = get(&R->kind[1][i]);
-        (&all.all)[i] = get(&R->all[i]);
+        (&all.all)[i] = (&kind[0].all)[i] + (&kind[1].all)[i];
     }
     const float n[2] = {get(&R->tiles[0]), get(&R->tiles[1])};
     const float items = (float)(J.n_splits * J.n_parts);  // of a tile
-    // time of a launch over n tiles of the cost: its rounds of resident workgroups, at
-    // least one
-    auto launch = [&](float tiles, float cost, double resident) {
-        return cost * fmaxf(tiles, (float)resident / items);
+    // time of a launch over n tiles of the cost, at least a round of resident workgroups,
+    // which is shorter the fewer a CU has of them
+    auto launch_small = [&](float tiles, const RingCounts& counts) {
+        return small_ring_cost(K, counts) *
+               fmaxf(tiles, kAloneSmall * (float)J.resident_small / items);
+    };
+    auto launch_large = [&](float tiles, const RingCounts& counts, int* h) {
+        return large_ring_cost(K, counts, L, h) *
+               fmaxf(tiles, kAloneLarge * (float)J.resident_large / items);
     };
     int shift_own = 0;
-    const float small = launch(n[0] + n[1], small_ring_cost(K, all), J.resident_small);
-    const float large =
-        launch(n[0] + n[1], large_ring_cost(K, all, L, &shift), J.resident_large);
+    const float small = launch_small(n[0] + n[1], all);
+    const float large = launch_large(n[0] + n[1], all, &shift);
     unsigned mode = small <= large ? kRingSel16 : kRingSel64 + shift;
     if (kind[0].segs > 0.0f && kind[1].segs > 0.0f) {
-        const float mixed = launch(n[0], small_ring_cost(K, kind[0]), J.resident_small) +
-                            launch(n[1], large_ring_cost(K, kind[1], L, &shift_own),
-                                   J.resident_large);
-        if (mixed < kOwnGain * fminf(small, large))
+        const float mixed =
+            launch_small(n[0], kind[0]) + launch_large(n[1], kind[1], &shift_own);
+        if (mixed < (J.rings_used ? kOwnGainBatch : kOwnGain) * fminf(small, large))
             mode = kRingsOwn | (kRingSel64 + shift_own);
     }
     R->mode = mode;
