@@ -443,9 +443,7 @@ int reserve(radio_detector* det, const radio::DepositJob& J, hipStream_t s)
     return rc;
 }
 
-// Enqueue a deposit in its time slices.  Only the first (largest) slice can
-// grow the workspaces, so a later one cannot fail for memory after earlier
-// ones were enqueued.
+// Enqueue the deposit of a few particles: one launch, no workspace, no slices.
 int enqueue_few(radio_detector* det, const radio::DepositJob& J, hipStream_t s)
 {
     if (radio::launch_few(J, det->precision, det->n_cus, s) != hipSuccess)
@@ -455,6 +453,9 @@ int enqueue_few(radio_detector* det, const radio::DepositJob& J, hipStream_t s)
     return RADIO_OK;
 }
 
+// Enqueue a deposit in its time slices.  Only the first (largest) slice can
+// grow the workspaces, so a later one cannot fail for memory after earlier
+// ones were enqueued.
 int enqueue_deposit(radio_detector* det, const radio_chunk* k, hipStream_t s)
 {
     if (k->n_particles == 0 || k->n_steps == 0)
@@ -549,6 +550,7 @@ int enqueue_deposit_noalloc(radio_detector* det, const radio_chunk* k, hipStream
     const radio::DepositJob W = make_job(det, k);
     if (slice_scratch_bytes(W, det->precision, 1) > kScratchBytes)
         return RADIO_ETOOBIG;
+    // takes no scratch, but what is too large is so for every number of particles
     if (radio::few_particles(W))
         return enqueue_few(det, W, s);
     // the longest time slices that fit the scratch

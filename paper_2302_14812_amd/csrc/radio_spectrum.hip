@@ -431,7 +431,7 @@ __global__ __launch_bounds__(64) void spec_rows_q32_kernel(const double2* __rest
 // transforms of up to 2 kFftTile slots
 // ---------------------------------------------------------------------------
 
-// The whole spectrum of C = min(kFftTile / N, 64) cells at a time in one kernel:
+// The whole spectrum of C = min(2^LGT / N, 64) cells at a time in one kernel:
 // a slot is read once (from the detector's E beside B: 48 bytes for 24), its
 // |E|^2 summed for dI/dOmega, both signals transformed in LDS, and the power
 // stored and added up over the workgroup's cells.  Persistent workgroups, two a CU:

@@ -1,12 +1,10 @@
-"""The large slot ring where a segment crosses several slots: field jumps in the
-mixed modes, slot values in the double mode and the linear hold, and runs staged
-in shorter stretches the more slots they span.
+"""The large slot ring where a segment crosses several slots, with runs staged in
+shorter stretches the more slots they span.
 
 The plasma-mirror sheet over ten periods in ever fewer steps crosses ~1.6 (250
 steps) to ~34 (12 steps) of 1024 slots a segment, from a whole run per stretch to
 one segment, and beyond what the ring holds at all.  Bars: the parity bars; slots
-no segment reaches read exactly zero (a sum of jumps starts again where no run
-is open).
+no segment reaches read exactly zero.
 """
 import numpy as np
 import pytest

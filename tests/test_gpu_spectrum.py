@@ -27,8 +27,8 @@ def rel_l2(a, b):
     return float(np.linalg.norm(a - b)) / (nb if nb > 0 else 1.0)
 
 
-# transform sizes: one LDS tile (up to 2048); the two-step transform with both
-# signals of a cell per tile in both steps (4096, 8192), with one signal per
+# transform sizes: one pass a cell (up to 4096); the two-step transform with both
+# signals of a cell per tile in both steps (8192), with one signal per
 # column tile (2^21), and with one signal per tile in both steps (2^22); the
 # radix-2 passes beyond 2^22
 @pytest.mark.parametrize("n_t,n_fft,precision,n_side", [
