@@ -1095,6 +1095,10 @@ constexpr RingCost kRingCost[3] = {
     {2.6f, 2.0f, 1.0f, 310.0f, 3.4f, 1.8f, 22.0f, 230.0f},   // mixed
     {2.7f, 2.2f, 1.0f, 720.0f, 3.6f, 2.2f, 36.0f, 350.0f}};  // compensated: two adds a
                                                              // component, the first returning
+// the linear hold's second field, with either ring: behind it more of the adds hide (300
+// electrons x 1024 steps x 64 x 64 cells, mixed: small ring 6.5 ms, large 7.9; with the
+// default hold both 6.3)
+constexpr float kLinearField = 1.3f;
 // what each tile's own ring has to gain: in a batch the other pairs fill its launches
 constexpr float kOwnGain = 0.88f, kOwnGainBatch = 0.96f;
 // a round's time with one workgroup a CU, of that with all that are resident (200 electrons
@@ -2359,9 +2363,13 @@ hipError_t launch_ring_choice(const DepositJob& job, int mode, hipStream_t s)
         return hipSuccess;
     const int64_t each = (job.n_tiles + kChoiceBlocks - 1) / kChoiceBlocks;
     const dim3 grid((unsigned)((job.n_tiles + each - 1) / each));
+    RingCost cost = kRingCost[mode];
+    if (job.hold == 2) {
+        cost.small += kLinearField;
+        cost.large += kLinearField;
+    }
     auto kernel = job.run_l == 16 ? ring_choice_kernel<16> : ring_choice_kernel<8>;
-    hipLaunchKernelGGL(kernel, grid, dim3(256), 0, s, job, (int64_t)rec_bytes(mode),
-                       kRingCost[mode], each);
+    hipLaunchKernelGGL(kernel, grid, dim3(256), 0, s, job, (int64_t)rec_bytes(mode), cost, each);
     return hipGetLastError();
 }
 
